@@ -26,11 +26,12 @@ inline bool dtype_ok(gt_dtype_t t) { return t == GT_F32 || t == GT_BF16; }
 
 inline bool scale_ok(float s) { return std::isfinite(s) && s > 0.0f; }
 
-// 16-byte spd loads are legal when every 16-key group of every row starts
-// 16-byte aligned.
-inline int spd_vec(const uint8_t* spd, int64_t ld, int64_t row_off, int64_t col_off) {
+// Whether every 16-key group of every spd row starts on a multiple of n bytes
+// (n = 16, 4).
+inline int spd_aligned(const uint8_t* spd, int64_t ld, int64_t row_off, int64_t col_off, int64_t bstride,
+                       unsigned n) {
   const uintptr_t base = reinterpret_cast<uintptr_t>(spd) + (uintptr_t)(row_off * ld + col_off);
-  return ((base & 15u) == 0 && (ld & 15) == 0) ? 1 : 0;
+  return base % n == 0 && ld % n == 0 && bstride % n == 0 ? 1 : 0;
 }
 
 inline gt_status_t launched(hipError_t e) { return e == hipSuccess ? GT_OK : GT_ERR_LAUNCH; }
@@ -75,7 +76,8 @@ static gt_status_t ring_impl(const void* q_shard, int64_t Sq, const void* k_shar
   a.table = table; a.n_buckets = n_buckets;
   a.o = o_part; a.lse = lse_part;
   a.H = H; a.Sq = Sq; a.Sk = Sk; a.scale = scale;
-  a.spd_vec = Sk > 0 ? spd_vec(spd, ld_spd, row_off, col_off) : 0;
+  a.spd_vec = Sk > 0 ? spd_aligned(spd, ld_spd, row_off, col_off, 0, 16) : 0;
+  a.spd_dw = Sk > 0 ? spd_aligned(spd, ld_spd, row_off, col_off, 0, 4) : 1;
   a.accumulate = accumulate;
   a.hpb = H; a.spd_bstride = 0;
   return launched(gt::launch_fwd(a, d, dtype == GT_BF16, true, static_cast<hipStream_t>(stream)));
@@ -123,7 +125,8 @@ static gt_status_t fwd_impl(const void* q, const void* k, const void* v, const u
   a.o = o; a.lse = lse;
   a.H = (int32_t)HT; a.Sq = N; a.Sk = N; a.scale = scale;
   a.hpb = H; a.spd_bstride = spd_bstride;
-  a.spd_vec = spd_vec(spd, N, 0, 0) && spd_bstride % 16 == 0;
+  a.spd_vec = spd_aligned(spd, N, 0, 0, spd_bstride, 16);
+  a.spd_dw = spd_aligned(spd, N, 0, 0, spd_bstride, 4);
   return launched(gt::launch_fwd(a, d, dtype == GT_BF16, dtype == GT_F32, static_cast<hipStream_t>(stream)));
 }
 
@@ -187,10 +190,11 @@ static gt_status_t bwd_impl(int32_t phase, const void* q, const void* k, const v
   a.H = H; a.Sq = N; a.Sk = N; a.scale = scale;
   a.row_off = 0; a.col_off = 0; a.accumulate = 0;
   a.hpb = Hh; a.spd_bstride = spd_bstride;
-  a.spd_vec = spd_vec(spd, N, 0, 0) && spd_bstride % 16 == 0;
+  a.spd_vec = spd_aligned(spd, N, 0, 0, spd_bstride, 16);
+  a.spd_dw = spd_aligned(spd, N, 0, 0, spd_bstride, 4);
   // The transpose is used only where its rows can be read 16 bytes at a time
   // and one key block's rows (256 of them) stay within 32-bit offsets.
-  a.spd_t = (spd_t && spd_vec(spd_t, N, 0, 0) && spd_bstride % 16 == 0 &&
+  a.spd_t = (spd_t && spd_aligned(spd_t, N, 0, 0, spd_bstride, 16) &&
              256 * N < (int64_t(1) << 31)) ? spd_t : nullptr;
   return launched(gt::launch_bwd(a, d, dtype == GT_BF16, phase, static_cast<hipStream_t>(stream)));
 }
@@ -324,7 +328,8 @@ gt_status_t gt_attn_bwd_ring_step(const void* q_shard, const void* o_shard, cons
   a.hpb = H; a.spd_bstride = 0;
   a.H = H; a.Sq = Sq; a.Sk = Sk; a.scale = scale;
   a.accumulate = 1;
-  a.spd_vec = spd_vec(spd, ld_spd, row_off, col_off);
+  a.spd_vec = spd_aligned(spd, ld_spd, row_off, col_off, 0, 16);
+  a.spd_dw = spd_aligned(spd, ld_spd, row_off, col_off, 0, 4);
   return launched(gt::launch_bwd(a, d, dtype == GT_BF16, -1, static_cast<hipStream_t>(stream)));
 }
 

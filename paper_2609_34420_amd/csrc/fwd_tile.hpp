@@ -50,20 +50,22 @@ __device__ __forceinline__ float exp_block(const float (&x)[16], bf16x8& p0, bf1
 // Softmax of one 32x32 score block s (accumulated as bias/scale + q.k) and
 // its P^T V product into acc. The exact path runs only when some lane's
 // block sum exceeds the limit (or is not finite) or a row has no reference.
+// MASK: keys at or past jrem (relative to the block) are padding; a block
+// of 32 keys or more (wave-uniform) is not masked.
 template <int D, bool MASK>
 __device__ __forceinline__ void softmax_pv(const f32x16& s, const bf16x8 (&vop)[2][D / 32],
-                                           int64_t jrem, float sl2, SoftmaxState& st,
+                                           int jrem, float sl2, SoftmaxState& st,
                                            f32x16 (&acc)[D / 32]) {
   constexpr int NCB = D / 32;
   const int g = (threadIdx.x >> 5) & 1;
   float x[16];
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const float xv = fmaf(s[r], sl2, st.mneg);
-    if constexpr (MASK)
-      x[r] = (16 * g + r < jrem) ? xv : -INFINITY;
-    else
-      x[r] = xv;
+  for (int r = 0; r < 16; ++r) x[r] = fmaf(s[r], sl2, st.mneg);
+  if constexpr (MASK) {
+    if (jrem < 32) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) x[r] = (16 * g + r < jrem) ? x[r] : -INFINITY;
+    }
   }
   bf16x8 p0, p1;
   float bs = exp_block(x, p0, p1);
@@ -103,8 +105,8 @@ __device__ __forceinline__ void softmax_pv(const f32x16& s, const bf16x8 (&vop)[
 // unit's Q^T.
 // NK: the 16-feature chunks that hold data (all D / 16, or fewer when the
 // source rows are narrower than the tile and the rest is zero).
-template <int D, int NK>
-__device__ __forceinline__ void issue_scores(const float* tab, const uint32_t (&w)[4], uint32_t lane4,
+template <int D, int NK, int NW>
+__device__ __forceinline__ void issue_scores(const float* tab, const uint32_t (&w)[NW], uint32_t lane4,
                                              const uint16_t* sK, const int (&koff)[D / 16], int kb,
                                              const bf16x8 (&q)[D / 16], f32x16& s) {
   load_bias(tab, w, lane4, s);

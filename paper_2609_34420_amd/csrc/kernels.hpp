@@ -25,6 +25,7 @@ struct FwdArgs {
   int64_t Sk;
   float scale;            // multiplies Q K^T
   int32_t spd_vec;        // every 16-byte spd group is 16-byte aligned
+  int32_t spd_dw;         // ... starts on a dword boundary
   int32_t accumulate;     // 1 (fp32 outputs only): o, lse hold a running merged state and
                           // this block is merged into it in place
   int32_t hpb;            // heads per sequence: "head" h of H is head h % hpb of sequence h / hpb
@@ -62,6 +63,7 @@ struct BwdArgs {
   int64_t Sk;
   float scale;
   int32_t spd_vec;        // every 16-byte spd group of the block is 16-byte aligned
+  int32_t spd_dw;         // ... starts on a dword boundary
   int32_t accumulate;     // 1: dq, dk, dv are fp32 and receive +=; dtable is not cleared
   int32_t hpb;            // heads per sequence: "head" h of H is head h % hpb of sequence h / hpb
                           // (table and dtable rows are per head, shared by the sequences)
@@ -92,6 +94,14 @@ struct MergeArgs {
 
 // Launchers return the hipError_t of the launch.
 hipError_t launch_fwd(const FwdArgs& a, int d, bool bf16, bool out_f32, hipStream_t s);
+// bf16 forward on the matrix cores (D: tile width, DS: head dim), and the
+// number of key groups its workgroups are split into.
+template <int D, int DS, bool OUT_F32>
+hipError_t launch_fwd_mfma(const FwdArgs& a, hipStream_t s);
+int fwd_key_split(const FwdArgs& a, int D);
+// The split ks = 1, 2, .. max_split that finishes first, for workgroups of
+// rows1 / ks rows over tiles of min(64 ks, max_tile) columns.
+int pick_split(int64_t rows, int64_t cols, int64_t heads, int rows1, int max_tile, int max_split);
 // Sequences of at most 256 rows, N a multiple of 4 (bf16 in and out,
 // d <= 32, at most 127 buckets, spd rows 4-byte aligned): the persistent
 // whole-sequence forward.

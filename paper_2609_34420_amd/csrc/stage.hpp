@@ -41,11 +41,11 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc_n(const void* base, 
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, n, 0x00020000);
 }
 
-// Resource over rows [r0, min(r0 + 64, nrows)) of a row-major [nrows, D]
+// Resource over rows [r0, min(r0 + ROWS, nrows)) of a row-major [nrows, D]
 // bf16 tensor: the tile's rows past nrows read as zero.
-template <int D>
+template <int D, int ROWS = kTileRows>
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rsrc(const uint16_t* t, int64_t r0, int64_t nrows) {
-  const int64_t rows = nrows - r0 < kTileRows ? nrows - r0 : kTileRows;
+  const int64_t rows = nrows - r0 < ROWS ? nrows - r0 : ROWS;
   return make_rsrc_n(t + r0 * D, rows * D * 2);
 }
 
@@ -111,17 +111,17 @@ struct RowStage {
 
 // Direct global -> LDS copy (buffer_load_dwordx4 ... lds): each lane's 16
 // bytes land at the wave-uniform LDS base + 16 lane, and lanes past the
-// descriptor's range write zeros. A pair of tiles (64 rows x D bf16 each,
+// descriptor's range write zeros. A pair of tiles (ROWS rows x D bf16 each,
 // one descriptor per tensor) is split into 1 KiB blocks handed to the NW
 // waves in order; within a block, lane l fills LDS chunk l % (D/8) of tile
 // row (block row 0) + l / (D/8), so it reads the logical chunk that the
 // swizzle stores there. Source rows of DS < D features leave the chunks
 // past DS zero.
-template <int D, int NW, int DS = D>
+template <int D, int NW, int DS = D, int ROWS = kTileRows>
 struct TileDma {
   static constexpr int ROWB = D * 2;
   static constexpr int RPB = 1024 / ROWB;              // rows per block
-  static constexpr int NBLK = kTileRows * ROWB / 1024; // blocks per tensor
+  static constexpr int NBLK = ROWS * ROWB / 1024;      // blocks per tensor
   static constexpr int BPW = 2 * NBLK / NW;            // blocks per wave
   static_assert(2 * NBLK % NW == 0, "blocks must divide evenly over the waves");
   static constexpr int NLOADS = BPW;                   // vector-memory ops per wave per tile pair
@@ -230,7 +230,8 @@ __device__ __forceinline__ void fill_lane_table(float* tab, const float* table_h
 
 // Bias entries of this lane's 16 keys (4 spd words) loaded into a score
 // accumulator: entry address 256 b + 4 lane from one byte permute.
-__device__ __forceinline__ void load_bias(const float* tab, const uint32_t (&w)[4], uint32_t lane4,
+template <int NW>
+__device__ __forceinline__ void load_bias(const float* tab, const uint32_t (&w)[NW], uint32_t lane4,
                                           f32x16& s) {
   const uint8_t* tb = reinterpret_cast<const uint8_t*>(tab);
 #pragma unroll

@@ -123,3 +123,42 @@ def test_histogram_fixed_point_range():
     below 2^63 for every N the stride limit admits."""
     terms = 2 * 8 * K_MAX_LD
     assert terms * 2 ** 30 < 2 ** 63
+
+
+@pytest.mark.parametrize("Sk", [16, 17, 31, 64, 100, 127, 130])
+@pytest.mark.parametrize("addr", [0, 1, 2, 3, 5, 14, 15])
+def test_spd_groups_at_any_address(Sk, addr):
+    """Forward and dQ: the group of 16 keys from key j of a row at byte `addr`
+    of a buffer that ends with the row. Every group but the row's last ones
+    is loaded as 16 bytes (dword-aligned rows) or as the 5 dwords that hold
+    it, shifted by its address mod 4; in the last tile the group starts at
+    min(j, Sk - 16), its fifth dword is read only if it holds a byte of the
+    group, and the group is moved down by j - (Sk - 16) bytes. Every key's
+    byte arrives in place and no dword without a byte of the row is read."""
+    row = [(7 * j + 3) % 251 + 1 for j in range(Sk)]
+    buf = [0] * addr + row
+    end4 = (len(buf) + 3) // 4 * 4             # the last byte's dword
+    buf += [0xEE] * (end4 - len(buf))
+
+    def dwords(a, n):
+        assert a % 4 == 0 and 0 <= a and a + 4 * n <= end4, (a, n)
+        return buf[a:a + 4 * n]
+
+    tile = 64
+    for t in range((Sk + tile - 1) // tile):
+        last = (t + 1) * tile >= Sk
+        for j in range(t * tile, t * tile + tile, 16):
+            if last:
+                a = addr + min(j, Sk - 16)
+                w = dwords(a & ~3, 4) + dwords((a & ~3) + (16 if a & 3 else 12), 1)
+            else:
+                a = addr + j
+                w = dwords(a & ~3, 5)
+            w = w[a & 3:(a & 3) + 16]          # v_alignbyte over the 5 dwords
+            drop = j - (Sk - 16) if last and Sk - 16 < j < Sk else 0
+            assert 0 <= drop < 16
+            w = w[drop:] + [0] * drop
+            n = max(0, min(16, Sk - j))
+            assert w[:n] == row[j:j + n]
+            if a % 4 == 0 and not last:        # the aligned kernels' single load
+                assert dwords(a, 4)[:n] == row[j:j + n]
