@@ -18,6 +18,12 @@
 //     (exact to about 2^-25 of Dlt), with the accumulator started at zero.
 // The score and dP products of the next 32-key block are issued before the
 // current block's element work, so the matrix cores overlap it.
+//
+// Key split (KS) and sizes (SpdRows): as in the forward (fwd_mfma.hpp); the
+// key groups' dQ partials are added through LDS at the end, in a fixed order.
+// H = 8, d = 64: N = 4000 (H = 4) 97 / 61 / 40 us with KS = 1 / 2 / 4, N = 2708
+// 71 / 46 / 56, N = 16384 870 / 1001 / 1105. Sizes that are no multiple of 16
+// took byte loads before: N = 7651 1244 -> 218 us, N = 2708 at d = 16 355 -> 30.
 #include <type_traits>
 
 #include "common.hpp"
@@ -30,8 +36,6 @@ namespace {
 
 constexpr int kWaves = 8;
 constexpr int kThreads = kWaves * 64;
-constexpr int kBC = 64;            // keys per LDS tile
-constexpr int kKB = kBC / 32;      // 32-key blocks per tile
 
 // Per-lane LDS element offsets of the operand reads (tile-relative; 32-key
 // block and 8-key step offsets are immediates). K and V rows share one
@@ -62,8 +66,8 @@ struct DqLane {
 
 // Score and dP products of one 32-key block (key block kb of a staged tile)
 // over the NK 16-feature chunks that hold data.
-template <int D, int NK>
-__device__ __forceinline__ void issue_block(const float* tab, const uint32_t (&w)[4], uint32_t lane4,
+template <int D, int NK, int NW>
+__device__ __forceinline__ void issue_block(const float* tab, const uint32_t (&w)[NW], uint32_t lane4,
                                             const uint16_t* sK, const uint16_t* sV,
                                             const DqOffsets<D>& off, int kb, const DqLane<D>& ln,
                                             f32x16& s, f32x16& dp) {
@@ -86,18 +90,47 @@ __device__ __forceinline__ void read_kt(const uint16_t* sK, const DqOffsets<D>& 
       kt[q][cb] = lds_tr_operand(sK + (kb * 32 + 8 * q) * D, off.kt[0][cb], off.kt[1][cb]);
 }
 
-// dS^T of one block and dQ^T += K^T dS^T. MASK: keys at or past jrem (relative
-// to the block) are padding.
-template <int D, bool MASK>
-__device__ __forceinline__ void block_dq(const f32x16& s, const f32x16& dp, const bf16x8 (&kt)[2][D / 32],
-                                         int64_t jrem, float sl2, float mlse2, f32x16 (&acc)[D / 32]) {
+// The products of block kb (as issue_block), the element work of the previous
+// block (s, dp; its K^T operands kt) and that block's dQ^T += K^T dS^T. The
+// fences keep the scheduler from sinking the products below the element work
+// (headline shape: 58.5 ms without them, 56.4 with; element work pinned
+// between the products by hand 57.6). MASK:
+// keys at or past jrem (relative to the previous block) are padding; a block
+// of 32 keys or more (wave-uniform) is not masked.
+template <int D, int NK, bool MASK, int NW>
+__device__ __forceinline__ void block_dq(const float* tab, const uint32_t (&w)[NW], uint32_t lane4,
+                                         const uint16_t* sK, const uint16_t* sV, const DqOffsets<D>& off, int kb,
+                                         const DqLane<D>& ln, f32x16& sn, f32x16& dpn, const f32x16& s,
+                                         const f32x16& dp, const bf16x8 (&kt)[2][D / 32], int jrem, float sl2,
+                                         f32x16 (&acc)[D / 32]) {
   const int g = (threadIdx.x >> 5) & 1;
   float ds[16];
+  auto element = [&](int r) { ds[r] = exp2_fast(fmaf(s[r], sl2, ln.mlse2)) * dp[r]; };
+  load_bias(tab, w, lane4, sn);
+  dpn = mfma32(ln.ones, ln.dlt, zero_f32x16());
+  bf16x8 kx = lds_b128(sK + kb * 32 * D + off.row[0]), vx = lds_b128(sV + kb * 32 * D + off.row[0]);
+  sched_fence();
+  constexpr int E = 8 / NK;            // elements per product
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    float pv = exp2_fast(fmaf(s[r], sl2, mlse2));
-    if constexpr (MASK) pv = (16 * g + r < jrem) ? pv : 0.0f;
-    ds[r] = pv * dp[r];
+  for (int kc = 0; kc < NK; ++kc) {
+    const bf16x8 kc0 = kx, vc0 = vx;
+    if (kc + 1 < NK) {
+      kx = lds_b128(sK + kb * 32 * D + off.row[kc + 1]);
+      vx = lds_b128(sV + kb * 32 * D + off.row[kc + 1]);
+    }
+    sn = mfma32(kc0, ln.qf[kc], sn);
+#pragma unroll
+    for (int e = 0; e < E; ++e) element(2 * kc * E + e);
+    dpn = mfma32(vc0, ln.df[kc], dpn);
+#pragma unroll
+    for (int e = 0; e < E; ++e) element((2 * kc + 1) * E + e);
+    sched_fence();
+  }
+  if constexpr (MASK) {
+    if (jrem < 32) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) ds[r] = (16 * g + r < jrem) ? ds[r] : 0.0f;
+    }
   }
 #pragma unroll
   for (int q = 0; q < 2; ++q) {
@@ -108,24 +141,29 @@ __device__ __forceinline__ void block_dq(const f32x16& s, const f32x16& dp, cons
 }
 
 // D: the tile's head dim (32 or 64); DS <= D: the head dim of the tensors
-// (8 and 16 run on 32-wide tiles whose extra features are zero). VEC: spd
-// rows are 16-byte aligned. FULL: VEC and Sk a multiple of the key tile, so
-// every spd group is loaded whole and no tile needs masking.
-template <int D, int DS, bool VEC, bool FULL>
+// (8 and 16 run on 32-wide tiles whose extra features are zero).
+template <int D, int DS, int KS, SpdRows ROWS>
 __global__ __launch_bounds__(kThreads, 1) void bwd_dq_bf16_kernel(BwdArgs a) {
+  constexpr bool RAG = ROWS != kWhole;
   constexpr int NKC = D / 16;
   constexpr int NKS = (DS + 15) / 16;   // feature chunks that hold data
   constexpr int NCB = D / 32;
-  constexpr int BR = kWaves * 32;
-  using Dma = TileDma<D, kWaves, DS>;     // K and V
-  static_assert(kBC == kTileRows, "key tile is one staged tile");
+  constexpr int NQW = kWaves / KS;      // waves per key group
+  constexpr int BR = NQW * 32;          // queries per workgroup
+  constexpr int TR = split_tile_rows<D, KS>();
+  constexpr int KB = TR / (32 * KS);    // 32-key blocks per wave and tile
+  static_assert(KB == 1 || KB == 2, "one or two key blocks per wave and tile");
+  static_assert(RAG || KS == 1, "the key-split kernels take every size");
+  using Dma = TileDma<D, kWaves, DS, TR>;   // K and V
 
-  __shared__ __attribute__((aligned(16))) uint16_t sK0[kBC * D], sK1[kBC * D], sK2[kBC * D];
-  __shared__ __attribute__((aligned(16))) uint16_t sV0[kBC * D], sV1[kBC * D], sV2[kBC * D];
+  __shared__ alignas(kStageAlign<D, TR>) uint16_t sK0[TR * D], sK1[TR * D], sK2[TR * D];
+  __shared__ alignas(kStageAlign<D, TR>) uint16_t sV0[TR * D], sV1[TR * D], sV2[TR * D];
   __shared__ __attribute__((aligned(16))) float sTab[kLaneTableFloats];
 
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = wave_id();
+  const int ks = KS == 1 ? 0 : wave / NQW;         // key group
+  const int qw = KS == 1 ? wave : wave % NQW;      // query wave
   const int col = lane & 31, g = lane >> 5;
   const uint32_t lane4 = (uint32_t)lane * 4u;
 
@@ -133,7 +171,12 @@ __global__ __launch_bounds__(kThreads, 1) void bwd_dq_bf16_kernel(BwdArgs a) {
   const int64_t lid = xcd_remap(blockIdx.x, nqb * a.H);
   const int h = (int)(lid % a.H);
   const int64_t qblk = lid / a.H;
-  const int64_t qbase = qblk * BR + (int64_t)wave * 32;
+  const int64_t qbase = qblk * BR + (int64_t)qw * 32;
+  // a wave whose rows all lie past Sq only takes its share of the copies,
+  // waits and barriers
+  const bool active = !RAG || qbase < a.Sq;
+  constexpr int kOff = KB * 32;                    // keys per group and tile
+  const int goff = ks * kOff * D;                  // the group's rows in a staged tile
 
   fill_lane_table(sTab, a.table + (int64_t)table_row(a, h) * a.n_buckets, a.n_buckets, a.scale, kThreads);
 
@@ -177,150 +220,164 @@ __global__ __launch_bounds__(kThreads, 1) void bwd_dq_bf16_kernel(BwdArgs a) {
 #pragma unroll
   for (int cb = 0; cb < NCB; ++cb) acc[cb] = zero_f32x16();
 
-  // spd bytes of key group j..j+15 of the lane's query row: one 16-byte raw
-  // buffer load, or byte loads for the partial last tile and unaligned
-  // slices.
   const int64_t ld = a.ld_spd;
   const int64_t rb = qbase < a.Sq ? qbase : a.Sq - 1;
-  const __amdgpu_buffer_rsrc_t rs = make_rsrc(seq_spd(a, h) + (a.row_off + rb) * ld + a.col_off);
-  const uint32_t voff = (uint32_t)((qrow - rb) * ld) + 16u * g;
-  const int64_t ntiles = (a.Sk + kBC - 1) / kBC;
-  auto fetch_spd = [&](int64_t tt, uint32_t (&w)[kKB][4]) {
-    const int64_t jt = (tt < ntiles ? tt : ntiles - 1) * kBC;
-    if (FULL || (VEC && jt + kBC <= a.Sk)) {
-#pragma unroll
-      for (int kb = 0; kb < kKB; ++kb) buf_u128(rs, voff, (uint32_t)(jt + kb * 32), w[kb]);
-    } else {
-      const uint8_t* row = seq_spd(a, h) + (a.row_off + qrow) * ld + a.col_off;
-#pragma unroll
-      for (int kb = 0; kb < kKB; ++kb) load_spd16_bytes(row, jt + kb * 32 + 16 * g, a.Sk, w[kb]);
-    }
-  };
+  using Spd = SpdStream<ROWS, TR>;
+  const Spd spd(seq_spd(a, h) + (a.row_off + rb) * ld + a.col_off, a.Sk, ks * kOff, g);
+  const typename Spd::Row srow = spd.row((qrow - rb) * ld);
+  const int64_t ntiles = spd.ntiles;
 
   const DqOffsets<D> off;
   const Dma dma(wave);
-  constexpr int SPD_LOADS = kKB;
+  constexpr int SPD_LOADS = KB * Spd::OPS;   // of one tile
 #define GT_DQ_STAGE(S_, K_, V_)                                                                 \
   uint16_t* K_ = (S_) == 0 ? sK0 : ((S_) == 1 ? sK1 : sK2);                                   \
   uint16_t* V_ = (S_) == 0 ? sV0 : ((S_) == 1 ? sV1 : sV2);
   auto copy_tile = [&](int64_t tt, auto stagec) {
     constexpr int S = decltype(stagec)::value;
     GT_DQ_STAGE(S, k_s, v_s)
-    const int64_t j_ = (tt < ntiles ? tt : ntiles - 1) * kBC;
-    dma.load(tile_rsrc<DS>(kh, j_, a.Sk), tile_rsrc<DS>(vh, j_, a.Sk), k_s, v_s);
+    const int64_t j_ = (tt < ntiles ? tt : ntiles - 1) * TR;
+    dma.load(tile_rsrc<DS, TR>(kh, j_, a.Sk), tile_rsrc<DS, TR>(vh, j_, a.Sk), k_s, v_s);
   };
   using S0 = std::integral_constant<int, 0>;
   using S1 = std::integral_constant<int, 1>;
   using S2 = std::integral_constant<int, 2>;
+  using P0 = std::integral_constant<int, 0>;
+  using P1 = std::integral_constant<int, 1>;
+  using Main = std::false_type;
+  using End = std::integral_constant<bool, RAG>;
 
-  if constexpr (FULL) {
-    // K/V tile t in stage t % 3 (copied two tiles ahead); spd words of tile
-    // t in register set t % 2 (fetched one tile ahead).
-    uint32_t wA[kKB][4], wB[kKB][4];
-    using P0 = std::integral_constant<int, 0>;
-    using P1 = std::integral_constant<int, 1>;
-    f32x16 s0, dp0;     // products of the current tile's first key block
-    if (ntiles > 0) {
-      copy_tile(0, S0());
-      copy_tile(1, S1());
-      copy_tile(2, S2());
-      fetch_spd(0, wA);
-      fetch_spd(1, wB);
-      wait_vmcnt<0>();
-      __syncthreads();     // table, tiles 0..2
-      issue_block<D, NKS>(sTab, wA[0], lane4, sK0, sV0, off, 0, ln, s0, dp0);
-    }
-    // Tile t: products of key block 1 issued, then block 0's element work
-    // and dQ product; block 1's K^T operands read; spd words of tile t + 2
-    // fetched into the freed set; tile boundary (tile t + 1 landed, barrier,
-    // stage refilled with tile t + 3); tile t + 1's block-0 products issued;
-    // block 1's element work and dQ product.
-    auto step = [&](int64_t t, auto stagec, auto setc) {
-      constexpr int S = decltype(stagec)::value;
-      constexpr int SN = (S + 1) % 3;
-      constexpr int P = decltype(setc)::value;
-      GT_DQ_STAGE(S, k_s, v_s)
-      GT_DQ_STAGE(SN, k_n, v_n)
-      auto& w = P == 0 ? wA : wB;
-      auto& w_n = P == 0 ? wB : wA;
-      f32x16 s1, dp1;
-      bf16x8 kt[2][NCB];
-      issue_block<D, NKS>(sTab, w[1], lane4, k_s, v_s, off, 1, ln, s1, dp1);
-      read_kt<D>(k_s, off, 0, kt);
-      block_dq<D, false>(s0, dp0, kt, kBC, sl2, ln.mlse2, acc);
-      read_kt<D>(k_s, off, 1, kt);
-      fetch_spd(t + 2, w);
-      sched_fence();
-      wait_vmcnt<SPD_LOADS + Dma::NLOADS>();
-      __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): this wave's reads of stage S done
-      __builtin_amdgcn_s_barrier();
-      copy_tile(t + 3, stagec);
-      sched_fence();
-      issue_block<D, NKS>(sTab, w_n[0], lane4, k_n, v_n, off, 0, ln, s0, dp0);
-      block_dq<D, false>(s1, dp1, kt, kBC, sl2, ln.mlse2, acc);
-    };
-    int64_t t = 0;
-    for (; t + 6 <= ntiles; t += 6) {
-      step(t, S0(), P0());
-      step(t + 1, S1(), P1());
-      step(t + 2, S2(), P0());
-      step(t + 3, S0(), P1());
-      step(t + 4, S1(), P0());
-      step(t + 5, S2(), P1());
-    }
-    if (t < ntiles) step(t, S0(), P0());
-    if (t + 1 < ntiles) step(t + 1, S1(), P1());
-    if (t + 2 < ntiles) step(t + 2, S2(), P0());
-    if (t + 3 < ntiles) step(t + 3, S0(), P1());
-    if (t + 4 < ntiles) step(t + 4, S1(), P0());
-  } else {
-    // Ragged or unaligned: spd words fetched two tiles ahead in three sets,
-    // one tile per step, every wait drains the loads.
-    uint32_t w0[kKB][4], w1[kKB][4], w2[kKB][4];
-    if (ntiles > 0) {
-      copy_tile(0, S0());
-      fetch_spd(0, w0);
-      copy_tile(1, S1());
-      fetch_spd(1, w1);
+  // K/V tile t in stage t % 3 (copied two tiles ahead); spd words of tile t
+  // in register set t % 2 (fetched one tile ahead).
+  uint32_t w[2][KB][Spd::NWD];
+  f32x16 s0, dp0;     // products of the current tile's first key block
+  if (ntiles > 0) {
+    copy_tile(0, S0());
+    copy_tile(1, S1());
+    copy_tile(2, S2());
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+#pragma unroll
+      for (int kb = 0; kb < KB; ++kb) spd.fetch(p, srow, kb, w[p][kb]);
+    if (spd.tiny()) {
+      const uint8_t* row = seq_spd(a, h) + (a.row_off + qrow) * ld + a.col_off;
+#pragma unroll
+      for (int kb = 0; kb < KB; ++kb)
+        load_spd16_bytes(row, ks * kOff + kb * 32 + 16 * g, a.Sk, w[0][kb]);
     }
     wait_vmcnt<0>();
-    __syncthreads();     // table, and the copy of tile 0
-    auto step = [&](int64_t t, auto stagec, auto maskc) {
-      constexpr int S = decltype(stagec)::value;
-      constexpr bool MASK = decltype(maskc)::value;
-      GT_DQ_STAGE(S, k_s, v_s)
-      copy_tile(t + 2, std::integral_constant<int, (S + 2) % 3>());
-      fetch_spd(t + 2, S == 0 ? w2 : (S == 1 ? w0 : w1));
-      sched_fence();
-      auto& w = S == 0 ? w0 : (S == 1 ? w1 : w2);
-      const int64_t jrem = a.Sk - t * kBC;
-#pragma unroll
-      for (int kb = 0; kb < kKB; ++kb) {
-        f32x16 s, dp;
-        bf16x8 kt[2][NCB];
-        issue_block<D, NKS>(sTab, w[kb], lane4, k_s, v_s, off, kb, ln, s, dp);
-        read_kt<D>(k_s, off, kb, kt);
-        block_dq<D, MASK>(s, dp, kt, jrem - kb * 32, sl2, ln.mlse2, acc);
-      }
-      wait_vmcnt<0>();
-      __builtin_amdgcn_s_barrier();
-    };
-    using Full = std::false_type;
-    using Part = std::true_type;
-    const int64_t nfull = a.Sk / kBC;
-    int64_t t = 0;
-    for (; t + 3 <= nfull; t += 3) {
-      step(t, S0(), Full());
-      step(t + 1, S1(), Full());
-      step(t + 2, S2(), Full());
+    __syncthreads();     // table, tiles 0..2
+    if (active) {
+      spd.ready(0, RAG, srow, 0, w[0][0]);
+      issue_block<D, NKS>(sTab, w[0][0], lane4, sK0 + goff, sV0 + goff, off, 0, ln, s0, dp0);
     }
-    if (t < ntiles) step(t, S0(), Part());
-    if (t + 1 < ntiles) step(t + 1, S1(), Part());
-    if (t + 2 < ntiles) step(t + 2, S2(), Part());
+  }
+  // Tile t: products of key block 1 issued, then block 0's element work
+  // and dQ product; block 1's K^T operands read; spd words of tile t + 2
+  // fetched into the freed set; tile boundary (tile t + 1 landed, barrier,
+  // stage refilled with tile t + 3); tile t + 1's block-0 products issued;
+  // block 1's element work and dQ product. With one block per tile, the next
+  // tile's products are issued before its element work.
+  auto step = [&](int64_t t, auto stagec, auto setc, auto endc) {
+    constexpr int S = decltype(stagec)::value;
+    constexpr int SN = (S + 1) % 3;
+    constexpr bool END = decltype(endc)::value;
+    GT_DQ_STAGE(S, k_s, v_s)
+    GT_DQ_STAGE(SN, k_n, v_n)
+    if (!active) {
+      wait_vmcnt<Dma::NLOADS>();
+      __builtin_amdgcn_s_barrier();
+      copy_tile(t + 3, stagec);
+      return;
+    }
+    k_s += goff;
+    v_s += goff;
+    const int jrem = END ? (int)(a.Sk - t * TR) - ks * kOff : 0;
+    f32x16 s1, dp1;
+    bf16x8 kt[2][NCB];
+    auto& wt = w[decltype(setc)::value];
+    auto& wn = w[decltype(setc)::value ^ 1];
+    if constexpr (KB == 2) {
+      read_kt<D>(k_s, off, 0, kt);
+      spd.ready(t, END, srow, 1, wt[1]);
+      block_dq<D, NKS, END>(sTab, wt[1], lane4, k_s, v_s, off, 1, ln, s1, dp1, s0, dp0, kt, jrem, sl2, acc);
+      read_kt<D>(k_s, off, 1, kt);
+    } else {
+      s1 = s0;
+      dp1 = dp0;
+      read_kt<D>(k_s, off, 0, kt);
+    }
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) spd.fetch(t + 2, srow, kb, wt[kb]);
+    sched_fence();
+    wait_vmcnt<SPD_LOADS + Dma::NLOADS>();
+    __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): this wave's reads of stage S done
+    __builtin_amdgcn_s_barrier();
+    copy_tile(t + 3, stagec);
+    sched_fence();
+    spd.ready(t + 1, END, srow, 0, wn[0]);
+    block_dq<D, NKS, END>(sTab, wn[0], lane4, k_n + goff, v_n + goff, off, 0, ln, s0, dp0, s1, dp1, kt,
+                          jrem - (KB - 1) * 32, sl2, acc);
+  };
+  {
+    // the step before the last tile is an END step too: it makes that tile's
+    // first words ready
+    const int64_t nmain = RAG ? ntiles - 2 : ntiles;
+    int64_t t = 0;
+    for (; t + 6 <= nmain; t += 6) {
+      step(t, S0(), P0(), Main());
+      step(t + 1, S1(), P1(), Main());
+      step(t + 2, S2(), P0(), Main());
+      step(t + 3, S0(), P1(), Main());
+      step(t + 4, S1(), P0(), Main());
+      step(t + 5, S2(), P1(), Main());
+    }
+    if (t < ntiles) step(t, S0(), P0(), End());
+    if (t + 1 < ntiles) step(t + 1, S1(), P1(), End());
+    if (t + 2 < ntiles) step(t + 2, S2(), P0(), End());
+    if (t + 3 < ntiles) step(t + 3, S0(), P1(), End());
+    if (t + 4 < ntiles) step(t + 4, S1(), P0(), End());
+    if constexpr (RAG) {
+      if (t + 5 < ntiles) step(t + 5, S2(), P1(), End());
+      if (t + 6 < ntiles) step(t + 6, S0(), P0(), End());
+    }
   }
   wait_vmcnt<0>();     // drain the clamped copies issued past the last tile
 #undef GT_DQ_STAGE
 
+  if constexpr (KS > 1) {
+    // group ks + half's partial is added to group ks's through the table's LDS
+    constexpr int XW = NCB * 16 * 64;              // floats of one wave's accumulators
+    static_assert(XW * kWaves / 2 <= kLaneTableFloats, "the exchange fits the table");
+#pragma unroll
+    for (int half = KS / 2; half >= 1; half /= 2) {
+      __syncthreads();   // the last reads of the table or of the previous exchange
+      if (ks >= half && ks < 2 * half) {
+        float4* x = reinterpret_cast<float4*>(sTab + ((ks - half) * NQW + qw) * XW) + lane;
+#pragma unroll
+        for (int cb = 0; cb < NCB; ++cb)
+#pragma unroll
+          for (int u = 0; u < 4; ++u)
+            x[(cb * 4 + u) * 64] = make_float4(acc[cb][4 * u], acc[cb][4 * u + 1], acc[cb][4 * u + 2],
+                                               acc[cb][4 * u + 3]);
+      }
+      __syncthreads();
+      if (ks < half) {
+        const float4* x = reinterpret_cast<const float4*>(sTab + (ks * NQW + qw) * XW) + lane;
+#pragma unroll
+        for (int cb = 0; cb < NCB; ++cb)
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const float4 y = x[(cb * 4 + u) * 64];
+            acc[cb][4 * u] += y.x;
+            acc[cb][4 * u + 1] += y.y;
+            acc[cb][4 * u + 2] += y.z;
+            acc[cb][4 * u + 3] += y.w;
+          }
+      }
+    }
+    if (ks != 0) return;
+  }
   if (i >= a.Sq) return;
   if (a.accumulate) {   // fp32 partial of the query shard, accumulated across ring steps
     float* dqa = reinterpret_cast<float*>(a.dq) + hq + i * DS;
@@ -353,17 +410,30 @@ __global__ __launch_bounds__(kThreads, 1) void bwd_dq_bf16_kernel(BwdArgs a) {
   }
 }
 
+template <int D, int DS, int KS>
+void launch_dq_ks(const BwdArgs& a, hipStream_t s) {
+  constexpr int BR = kWaves / KS * 32;
+  const dim3 grid((unsigned)((a.Sq + BR - 1) / BR * a.H));
+  if (!a.spd_dw) {
+    hipLaunchKernelGGL((bwd_dq_bf16_kernel<D, DS, KS, kBytes>), grid, dim3(kThreads), 0, s, a);
+    return;
+  }
+  if constexpr (KS == 1) {
+    if (a.Sq % BR == 0 && a.Sk % split_tile_rows<D, KS>() == 0) {
+      hipLaunchKernelGGL((bwd_dq_bf16_kernel<D, DS, KS, kWhole>), grid, dim3(kThreads), 0, s, a);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((bwd_dq_bf16_kernel<D, DS, KS, kRagged>), grid, dim3(kThreads), 0, s, a);
+}
+
 template <int D, int DS>
 void launch_dq_t(const BwdArgs& a, hipStream_t s) {
-  constexpr int BR = kWaves * 32;
-  const int64_t nqb = (a.Sq + BR - 1) / BR;
-  const dim3 grid((unsigned)(nqb * a.H));
-  if (a.spd_vec && a.Sk % kBC == 0)
-    hipLaunchKernelGGL((bwd_dq_bf16_kernel<D, DS, true, true>), grid, dim3(kThreads), 0, s, a);
-  else if (a.spd_vec)
-    hipLaunchKernelGGL((bwd_dq_bf16_kernel<D, DS, true, false>), grid, dim3(kThreads), 0, s, a);
-  else
-    hipLaunchKernelGGL((bwd_dq_bf16_kernel<D, DS, false, false>), grid, dim3(kThreads), 0, s, a);
+  switch (pick_split(a.Sq, a.Sk, a.H, kWaves * 32, D == 64 ? 128 : 256, 4)) {
+    case 1: launch_dq_ks<D, DS, 1>(a, s); break;
+    case 2: launch_dq_ks<D, DS, 2>(a, s); break;
+    default: launch_dq_ks<D, DS, 4>(a, s); break;
+  }
 }
 
 }  // namespace

@@ -45,7 +45,7 @@
 // Before these kernels took every size, an N that is no multiple of 16 went
 // byte by byte: N = 7651 2298 us, N = 2708 at d = 16 677 us, now 175 and 30.
 //
-// Any size and alignment: see FwdRows below.
+// Any size and alignment: see SpdRows in stage.hpp.
 #pragma once
 #include <type_traits>
 
@@ -62,31 +62,17 @@ constexpr int kWaves = 8;
 constexpr int kThreads = kWaves * 64;
 constexpr int kQB = 2;             // 32-query blocks per wave
 
-// Keys per staged tile: 64 per key group, at most what three stages of K and
-// V leave LDS for beside the 64 KB table.
-template <int D, int KS>
-constexpr int fwd_tile_rows() { return 64 * KS < (D == 64 ? 128 : 256) ? 64 * KS : (D == 64 ? 128 : 256); }
-
-// Sizes and spd alignment a kernel takes. kWhole: Sq a multiple of the
-// workgroup's rows, Sk of the tile, spd rows on dword boundaries. kRagged:
-// any sizes, spd rows on dword boundaries; in the last tile, a group of 16 spd
-// bytes that would end past the row's last key is loaded as the row's last 16
-// bytes and shifted into place, and the scores past the last key are masked.
-// kBytes: any sizes and any spd address; each group is loaded as the 5 dwords
-// that hold it and aligned when its scores come up.
-enum FwdRows { kWhole = 0, kRagged = 1, kBytes = 2 };
-
 // D: the tile's head dim (32 or 64); DS <= D: the head dim of the tensors
 // (8 and 16 run on 32-wide tiles whose extra features are zero).
-template <int D, int DS, bool OUT_F32, int KS, FwdRows ROWS>
+template <int D, int DS, bool OUT_F32, int KS, SpdRows ROWS>
 __global__ __launch_bounds__(kThreads, 1) void fwd_bf16_kernel(FwdArgs a) {
-  constexpr bool RAG = ROWS != kWhole, BYTES = ROWS == kBytes;
+  constexpr bool RAG = ROWS != kWhole;
   constexpr int NKC = D / 16;
   constexpr int NKS = (DS + 15) / 16;   // feature chunks that hold data
   constexpr int NCB = D / 32;
   constexpr int NQW = kWaves / KS;      // waves per key group
   constexpr int BR = NQW * 32 * kQB;    // queries per workgroup
-  constexpr int TR = fwd_tile_rows<D, KS>();
+  constexpr int TR = split_tile_rows<D, KS>();
   constexpr int KB = TR / (32 * KS);    // 32-key blocks per wave and tile
   static_assert(KB == 1 || KB == 2, "one or two key blocks per wave and tile");
   static_assert(RAG || KS == 1, "the key-split kernels take every size");
@@ -95,8 +81,8 @@ __global__ __launch_bounds__(kThreads, 1) void fwd_bf16_kernel(FwdArgs a) {
   // Three-stage ring of K / V tiles, one array per stage so that no read of
   // one stage can be taken to alias the copy into another; the bias table,
   // one copy per lane: entry (b, lane) at float index 64 b + lane.
-  __shared__ __attribute__((aligned(16))) uint16_t sK0[TR * D], sK1[TR * D], sK2[TR * D];
-  __shared__ __attribute__((aligned(16))) uint16_t sV0[TR * D], sV1[TR * D], sV2[TR * D];
+  __shared__ alignas(kStageAlign<D, TR>) uint16_t sK0[TR * D], sK1[TR * D], sK2[TR * D];
+  __shared__ alignas(kStageAlign<D, TR>) uint16_t sV0[TR * D], sV1[TR * D], sV2[TR * D];
   __shared__ __attribute__((aligned(16))) float sTab[kLaneTableFloats];
 
   const int tid = threadIdx.x;
@@ -142,54 +128,14 @@ __global__ __launch_bounds__(kThreads, 1) void fwd_bf16_kernel(FwdArgs a) {
     }
   }
 
-  // spd bytes of key group j .. j + 15 of the lane's query row: one 16-byte
-  // raw buffer load (scalar base per wave, lane offset row * ld + 16 g,
-  // scalar key offset), NWD dwords.
-  constexpr int NWD = BYTES ? 5 : 4;
   const int64_t ld = a.ld_spd;
   const int64_t rb = qbase < a.Sq ? qbase : a.Sq - 1;
-  uint32_t rem;
-  const __amdgpu_buffer_rsrc_t rs = spd_rsrc(seq_spd(a, h) + (a.row_off + rb) * ld + a.col_off, rem);
-  uint32_t voff[kQB], vsh[kQB];
+  using Spd = SpdStream<ROWS, TR>;
+  const Spd spd(seq_spd(a, h) + (a.row_off + rb) * ld + a.col_off, a.Sk, ks * kOff, g);
+  typename Spd::Row srow[kQB];
 #pragma unroll
-  for (int qb = 0; qb < kQB; ++qb) {
-    voff[qb] = (uint32_t)((qrow[qb] - rb) * ld) + 16u * (uint32_t)g + (BYTES ? rem : 0u);
-    vsh[qb] = BYTES ? voff[qb] & 3u : 0u;
-    voff[qb] -= vsh[qb];
-  }
-  const int klast = (int)a.Sk - 16;                // first byte of a row's last 16
-  const int64_t ntiles = (a.Sk + TR - 1) / TR;
-  // first key of this lane half's group kb in the last tile
-  const int jend = (int)((ntiles - 1) * TR) + ks * kOff + 16 * g;
-  // offset (from column 16 g) that group kb of the last tile is loaded from
-  auto end_off = [&](int kb) { return (jend + kb * 32 < klast ? jend + kb * 32 : klast) - 16 * g; };
-  // Words of unit (key block kb, query block qb) of tile tt (clamped).
-  auto spd_of = [&](int64_t tt, int qb, int kb, uint32_t (&w)[NWD]) {
-    const int jt = (int)((tt < ntiles ? tt : ntiles - 1) * TR) + ks * kOff + kb * 32;
-    if (RAG && klast < 0) return;                  // fewer than 16 keys: loaded once, by bytes
-    if constexpr (BYTES) {
-      if (tt + 1 < ntiles)
-        load_spd5(rs, voff[qb], (uint32_t)jt, w);
-      else
-        load_spd5_end(rs, voff[qb] + vsh[qb] + (uint32_t)end_off(kb), w);
-    } else if constexpr (RAG) {
-      const int j = jt < klast - 16 * g ? jt : klast - 16 * g;
-      buf_u128(rs, voff[qb] + (uint32_t)j, rem, w);
-    } else {
-      buf_u128(rs, voff[qb], (uint32_t)jt + rem, w);
-    }
-  };
-  // Its words moved into place (bytes past Sk are masked later).
-  auto spd_ready = [&](int64_t tt, bool end, int qb, int kb, uint32_t (&w)[NWD]) {
-    if (RAG && end && tt + 1 >= ntiles) {
-      if (klast < 0) return;
-      const int j = jend + kb * 32;
-      if constexpr (BYTES) align_spd5(w, (vsh[qb] + (uint32_t)end_off(kb)) & 3u);
-      shift_spd16(w, j > klast && j < (int)a.Sk ? j - klast : 0);
-    } else if constexpr (BYTES) {
-      align_spd5(w, vsh[qb]);
-    }
-  };
+  for (int qb = 0; qb < kQB; ++qb) srow[qb] = spd.row((qrow[qb] - rb) * ld);
+  const int64_t ntiles = spd.ntiles;
 
   SoftmaxState sm[kQB];
   f32x16 acc[kQB][NCB];
@@ -204,7 +150,7 @@ __global__ __launch_bounds__(kThreads, 1) void fwd_bf16_kernel(FwdArgs a) {
 
   const FwdOffsets<D> off;
   const Dma dma(wave);
-  constexpr int SPD_LOADS = kQB * KB * (BYTES ? 2 : 1);   // of one tile
+  constexpr int SPD_LOADS = kQB * KB * Spd::OPS;   // of one tile
 #define GT_FWD_STAGE(S_, K_, V_)                                                                \
   uint16_t* K_ = (S_) == 0 ? sK0 : ((S_) == 1 ? sK1 : sK2);                                     \
   uint16_t* V_ = (S_) == 0 ? sV0 : ((S_) == 1 ? sV1 : sV2);
@@ -228,14 +174,14 @@ __global__ __launch_bounds__(kThreads, 1) void fwd_bf16_kernel(FwdArgs a) {
   // tile t + 1 are fetched as soon as its words of tile t have been used.
   // (H = 8, d = 64, N = 16384 and 16000: 660 us with the fetches together, 690
   // with two sets fetched unit by unit, 700-750 with one set.)
-  constexpr int NS = BYTES && D == 64 && KB == 2 ? 1 : 2;
-  uint32_t w[NS][kQB][KB][NWD];
+  constexpr int NS = Spd::BYTES && D == 64 && KB == 2 ? 1 : 2;
+  uint32_t w[NS][kQB][KB][Spd::NWD];
   // Score product of unit (kb, qb) of tile tt (set P) from staged keys k_t.
   auto scores = [&](int64_t tt, auto setc, auto endc, int qb, int kb, const uint16_t* k_t, f32x16& s) {
     auto& wu = w[decltype(setc)::value % NS][qb][kb];
-    spd_ready(tt, decltype(endc)::value, qb, kb, wu);
+    spd.ready(tt, decltype(endc)::value, srow[qb], kb, wu);
     issue_scores<D, NKS>(sTab, wu, lane4, k_t, off.k, kb, qf[qb], s);
-    if constexpr (NS == 1) spd_of(tt + 1, qb, kb, wu);
+    if constexpr (NS == 1) spd.fetch(tt + 1, srow[qb], kb, wu);
   };
   using Main = std::false_type;
   using End = std::integral_constant<bool, RAG>;
@@ -251,8 +197,8 @@ __global__ __launch_bounds__(kThreads, 1) void fwd_bf16_kernel(FwdArgs a) {
 #pragma unroll
       for (int qb = 0; qb < kQB; ++qb)
 #pragma unroll
-        for (int kb = 0; kb < KB; ++kb) spd_of(p, qb, kb, w[p][qb][kb]);
-    if (RAG && klast < 0) {
+        for (int kb = 0; kb < KB; ++kb) spd.fetch(p, srow[qb], kb, w[p][qb][kb]);
+    if (spd.tiny()) {
 #pragma unroll
       for (int qb = 0; qb < kQB; ++qb) {
         const uint8_t* row = seq_spd(a, h) + (a.row_off + qrow[qb]) * ld + a.col_off;
@@ -286,7 +232,7 @@ __global__ __launch_bounds__(kThreads, 1) void fwd_bf16_kernel(FwdArgs a) {
 #pragma unroll
         for (int qb = 0; qb < kQB; ++qb)
 #pragma unroll
-          for (int kb = 0; kb < KB; ++kb) spd_of(t + 2, qb, kb, w[decltype(setc)::value][qb][kb]);
+          for (int kb = 0; kb < KB; ++kb) spd.fetch(t + 2, srow[qb], kb, w[decltype(setc)::value][qb][kb]);
       }
     };
     if (!active) {
@@ -464,7 +410,7 @@ void launch_fwd_ks(const FwdArgs& a, hipStream_t s) {
     return;
   }
   if constexpr (KS == 1) {
-    if (a.Sq % BR == 0 && a.Sk % fwd_tile_rows<D, KS>() == 0) {
+    if (a.Sq % BR == 0 && a.Sk % split_tile_rows<D, KS>() == 0) {
       hipLaunchKernelGGL((fwd_bf16_kernel<D, DS, OUT_F32, KS, kWhole>), grid, dim3(kThreads), 0, s, a);
       return;
     }

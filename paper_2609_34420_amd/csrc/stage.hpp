@@ -241,4 +241,94 @@ __device__ __forceinline__ void load_bias(const float* tab, const uint32_t (&w)[
   }
 }
 
+// Sizes and spd alignment a query-stationary kernel takes. kWhole: the query
+// rows a multiple of the workgroup's, Sk of the tile, spd rows on dword
+// boundaries. kRagged: any sizes, spd rows on dword boundaries; in the last
+// tile, a group of 16 spd bytes that would end past the row's last key is
+// loaded as the row's last 16 bytes and shifted into place, and the scores
+// past the last key are masked. kBytes: any sizes and any spd address; each
+// group is loaded as the 5 dwords that hold it and aligned when its scores
+// come up.
+enum SpdRows { kWhole = 0, kRagged = 1, kBytes = 2 };
+
+// The spd words a wave of a query-stationary kernel streams: for the lane's
+// query rows, groups of 16 keys (lane half g: keys 16 g .. + 15 of each 32-key
+// block kb < KB) of the wave's part (from key `part` on) of every TR-key tile,
+// by raw buffer loads: scalar base per wave, lane offset row * ld + 16 g,
+// scalar key offset.
+template <SpdRows ROWS, int TR>
+struct SpdStream {
+  static constexpr bool RAG = ROWS != kWhole, BYTES = ROWS == kBytes;
+  static constexpr int NWD = BYTES ? 5 : 4;          // dwords of a group in flight
+  static constexpr int OPS = BYTES ? 2 : 1;          // vector-memory ops per group
+  struct Row { uint32_t voff, sh; };                 // a lane's row: offset, its address mod 4 (kBytes)
+
+  uint32_t rem = 0;                                  // kBytes: bytes from the resource's base to row0
+  __amdgpu_buffer_rsrc_t rs;
+  int64_t ntiles;
+  int part, g16, nkeys, klast, jend;
+
+  // row0: spd of the wave's first row and the block's first key.
+  __device__ __forceinline__ SpdStream(const uint8_t* row0, int64_t Sk, int part_, int g)
+      : rs(BYTES ? spd_rsrc(row0, rem) : make_rsrc(row0)), ntiles((Sk + TR - 1) / TR), part(part_), g16(16 * g),
+        nkeys((int)Sk), klast((int)Sk - 16), jend((int)((ntiles - 1) * TR) + part_ + 16 * g) {}
+  __device__ __forceinline__ Row row(int64_t bytes) const {    // bytes: from the wave's first row
+    Row r;
+    r.voff = (uint32_t)bytes + (uint32_t)g16 + (BYTES ? rem : 0u);
+    r.sh = BYTES ? r.voff & 3u : 0u;
+    r.voff -= r.sh;
+    return r;
+  }
+  // Fewer than 16 keys: the caller loads them once, by bytes.
+  __device__ __forceinline__ bool tiny() const { return RAG && klast < 0; }
+  // Offset (from column 16 g) that group kb of the last tile is loaded from.
+  __device__ __forceinline__ int end_off(int kb) const {
+    return (jend + kb * 32 < klast ? jend + kb * 32 : klast) - g16;
+  }
+  // Words of group kb of tile tt (clamped to the last).
+  __device__ __forceinline__ void fetch(int64_t tt, const Row& r, int kb, uint32_t (&w)[NWD]) const {
+    const int jt = (int)((tt < ntiles ? tt : ntiles - 1) * TR) + part + kb * 32;
+    if (tiny()) return;
+    if constexpr (BYTES) {
+      if (tt + 1 < ntiles)
+        load_spd5(rs, r.voff, (uint32_t)jt, w);
+      else
+        load_spd5_end(rs, r.voff + r.sh + (uint32_t)end_off(kb), w);
+    } else if constexpr (RAG) {
+      const int j = jt < klast - g16 ? jt : klast - g16;
+      buf_u128(rs, r.voff + (uint32_t)j, 0u, w);
+    } else {
+      buf_u128(rs, r.voff, (uint32_t)jt, w);
+    }
+  }
+  // Its words moved into w[0..3] (bytes past the last key are masked by the
+  // caller). end: tt may be the last tile.
+  __device__ __forceinline__ void ready(int64_t tt, bool end, const Row& r, int kb, uint32_t (&w)[NWD]) const {
+    if (RAG && end && tt + 1 >= ntiles) {
+      if (tiny()) return;
+      const int j = jend + kb * 32;
+      if constexpr (BYTES) align_spd5(w, (r.sh + (uint32_t)end_off(kb)) & 3u);
+      shift_spd16(w, j > klast && j < nkeys ? j - klast : 0);
+    } else if constexpr (BYTES) {
+      align_spd5(w, r.sh);
+    }
+  }
+};
+
+// Keys per staged tile of a query-stationary kernel whose 8 waves form KS key
+// groups: 64 per group, at most what three stages of K and V leave LDS for
+// beside the 64 KB table.
+template <int D, int KS>
+constexpr int split_tile_rows() { return 64 * KS < (D == 64 ? 128 : 256) ? 64 * KS : (D == 64 ? 128 : 256); }
+
+// Alignment of the K / V stages beside the 16-byte aligned table. LDS objects
+// are placed by decreasing alignment, then size: with the stages first, up to
+// 48 KB of them, every operand and table read reaches its object by the DS
+// immediate (16 bits) from one per-lane offset; with the table first the
+// stages lie past 64 KB and their addresses take some twenty registers, which
+// the wave of the 64-wide kernels does not have. 96 KB of stages do not fit
+// under the immediate either way: there the table goes first.
+template <int D, int TR>
+constexpr int kStageAlign = 6 * TR * D * 2 <= 49152 ? 128 : 16;
+
 }  // namespace gt
