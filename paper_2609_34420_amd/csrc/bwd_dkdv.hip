@@ -29,7 +29,16 @@
 // Query tiles (Q and dO row-major, statistics) are double buffered in LDS;
 // Q^T and dO^T are read with transposing LDS reads. The next tile's global
 // loads are in flight while the current one is computed, one barrier per
-// tile. spd bytes are fetched one 32-query sub-block ahead of their use.
+// tile. spd bytes, at any row address, are fetched one 32-query sub-block ahead of their use.
+//
+// Query split (QS): with 256 keys per workgroup a graph of a few thousand
+// nodes gives fewer workgroups than the chip has compute units. With QS = 2
+// or 4 the 8 waves are QS groups that share 256 / QS keys:
+// group qs takes the qs-th part of every query tile, and the groups' dK and dV
+// are added through LDS at the end, in a fixed order (the histogram is shared
+// by all waves as it is). H = 8, d = 64: N = 2000 101 / 61 / 40 us with QS = 1 /
+// 2 / 4, N = 2708 127 / 79 / 96, N = 11000 966 / 810 / 945, N = 16384 1495 / 1605 /
+// 1934.
 #include <type_traits>
 
 #include "common.hpp"
@@ -41,9 +50,17 @@ namespace gt {
 namespace {
 
 constexpr int kNW = 8;              // waves per workgroup
-constexpr int kBK = kNW * 32;       // keys per workgroup
-constexpr int kBQ = 64;             // queries per staged tile
 constexpr int kThreads = kNW * 64;
+// Queries per staged tile whose waves form QS query groups: 64 per group, 32
+// where two buffers of Q and dO would not fit below the table at 64 KiB (and
+// 64 in all for two groups at D = 64, which then fit with the statistics).
+template <int D, int QS>
+constexpr int dkdv_tile_rows() { return D == 64 && QS == 2 ? 64 : (QS == 1 ? 64 : 128); }
+
+// How a wave reads the spd bytes of its keys: kTrans: rows of spd_t; kRowsDw,
+// kRowsAny: rows of spd on dword boundaries, or at any address, transposed
+// through LDS.
+enum SpdRead { kTrans = 0, kRowsDw = 1, kRowsAny = 2 };
 // Table / histogram copies: lane & (CPY - 1); 32 copies (two lanes per copy)
 // in the 128-bucket layout, else 16.
 template <int NB>
@@ -55,54 +72,75 @@ constexpr int copies() { return NB <= 128 ? 32 : 16; }
 // copies. The per-element address register holds the absolute address of
 // the table entry (bucket, copy); the histogram entry is at a fixed
 // immediate offset (ENT * 8) from it. NB (128 or 256) bounds the byte
-// values the layout covers.
-template <int D>
+// values the layout covers. The statistics and the spd staging lie below the
+// table, or behind the histogram where the tiles take the whole 64 KiB.
+constexpr uint32_t kTabBase = 65536;
+template <int D, int BQ>
 struct DkdvTiles {
-  uint16_t q[2][kBQ * D];
-  uint16_t o[2][kBQ * D];
-  float init_s[2][kBQ];             // -LSE log2 e / (scale log2 e); -inf for empty rows
-  float init_p[2][kBQ];             // -Dlt 2^F
+  uint16_t q[2][BQ * D];
+  uint16_t o[2][BQ * D];
+};
+template <int BQ>
+struct DkdvRows {
+  float init_s[2][BQ];              // -LSE log2 e / (scale log2 e); -inf for empty rows
+  float init_p[2][BQ];              // -Dlt 2^F
   float red[3][kNW];
   uint8_t stage[kNW][1024];         // per wave: a 32 x 32 block of spd bytes (row-wise staging)
 };
-constexpr uint32_t kTabBase = 65536;
-template <int D, int NB>
-struct DkdvSmem : DkdvTiles<D> {
+template <int NB>
+struct DkdvTable {
   static constexpr int ENT = NB * copies<NB>();   // entry (b, c) = b * CPY + c
-  uint8_t pad[kTabBase - sizeof(DkdvTiles<D>)];
   uint2 tabw[ENT];                  // table copies (fp32 bits, 8-byte stride)
   unsigned long long hist[ENT];     // gradient histogram copies, same index
 };
+template <int D, int NB, int BQ, bool FULL = (sizeof(DkdvTiles<D, BQ>) == kTabBase)>
+struct DkdvSmem : DkdvTiles<D, BQ>, DkdvRows<BQ> {
+  uint8_t pad[kTabBase - sizeof(DkdvTiles<D, BQ>) - sizeof(DkdvRows<BQ>)];
+  DkdvTable<NB> t;
+};
+template <int D, int NB, int BQ>
+struct DkdvSmem<D, NB, BQ, true> : DkdvTiles<D, BQ> {
+  DkdvTable<NB> t;
+  DkdvRows<BQ> r;
+};
+template <int D, int NB, int BQ, bool FULL>
+__device__ __forceinline__ DkdvRows<BQ>& rows_of(DkdvSmem<D, NB, BQ, FULL>& sm) {
+  if constexpr (FULL)
+    return sm.r;
+  else
+    return sm;
+}
 
 // Per-lane LDS element offsets of the operand reads (tile-relative; the
-// 32-query sub-block and 8-query step offsets are immediates).
+// 32-query sub-block and 8-query step offsets are immediates). row0: the query
+// group's first row in a tile.
 template <int D>
 struct DkdvOffsets {
   int row[D / 16];        // Q / dO rows perm32(lane), feature chunk 2 kc + g
   int tr[2][D / 32];      // transposing reads h = 0, 1, feature block cb
-  __device__ __forceinline__ DkdvOffsets() {
+  __device__ __forceinline__ explicit DkdvOffsets(int row0) {
 #pragma unroll
-    for (int kc = 0; kc < D / 16; ++kc) row[kc] = row_operand_off<D>(kc);
+    for (int kc = 0; kc < D / 16; ++kc) row[kc] = row0 * D + row_operand_off<D>(kc);
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
-      for (int cb = 0; cb < D / 32; ++cb) tr[h][cb] = tr_operand_off<D>(h, cb);
+      for (int cb = 0; cb < D / 32; ++cb) tr[h][cb] = row0 * D + tr_operand_off<D>(h, cb);
   }
 };
 
 // A query tile in flight: Q and dO rows (rows past N read as zero; source
-// rows of DS < D features padded with zeros) and the statistics of its 64
+// rows of DS < D features padded with zeros) and the statistics of its
 // queries.
-template <int D, int DS>
+template <int D, int DS, int kBQ>
 struct QTileStage {
-  RowStage<D, kThreads, DS> q, o;
+  RowStage<D, kThreads, DS, kBQ> q, o;
   float stat;
 
   __device__ __forceinline__ void load(const uint16_t* qh, const uint16_t* oh, const float* lse2h,
                                        const float* dlth, int64_t i0, int64_t n) {
-    q.load(tile_rsrc<DS>(qh, i0, n));
-    o.load(tile_rsrc<DS>(oh, i0, n));
-    // every thread loads (two copies of the 128 values), clamped to row N-1
+    q.load(tile_rsrc<DS, kBQ>(qh, i0, n));
+    o.load(tile_rsrc<DS, kBQ>(oh, i0, n));
+    // every thread loads (copies of the 2 kBQ values), clamped to row N-1
     const int ts = (int)threadIdx.x & (2 * kBQ - 1);
     const int64_t i = i0 + (ts & (kBQ - 1));
     const int64_t ic = i < n ? i : n - 1;
@@ -112,7 +150,7 @@ struct QTileStage {
   // (-lse2 / (scale log2 e), -inf for padded rows so that P = 0) and of the
   // scaled dP (-Dlt 2^F).
   template <int BUF, int NB>
-  __device__ __forceinline__ void store(DkdvSmem<D, NB>& sm, int64_t i0, int64_t n, float inv_sl2,
+  __device__ __forceinline__ void store(DkdvSmem<D, NB, kBQ>& sm, int64_t i0, int64_t n, float inv_sl2,
                                         float sF) {
     q.store(sm.q[BUF]);
     o.store(sm.o[BUF]);
@@ -123,39 +161,12 @@ struct QTileStage {
       const int qi = t & (kBQ - 1);
       const bool in = i0 + qi < n;
       if (t < kBQ)
-        sm.init_s[BUF][qi] = in ? -st * inv_sl2 : -INFINITY;
+        rows_of(sm).init_s[BUF][qi] = in ? -st * inv_sl2 : -INFINITY;
       else
-        sm.init_p[BUF][qi] = in ? -st * sF : 0.0f;
+        rows_of(sm).init_p[BUF][qi] = in ? -st * sF : 0.0f;
     }
   }
 };
-
-// spd bytes of this lane's key for the 16 queries i_base + 16 g + r, by raw
-// buffer loads: a scalar base per sub-block, scalar row offsets r * ld and a
-// per-lane offset 16 g ld + key. QFULL (N a multiple of the query tile): every
-// row exists. Otherwise rows past n read the clamped row n-1 (their P is 0,
-// any bucket will do), branch-free.
-template <bool QFULL>
-__device__ __forceinline__ void load_bytes(const uint8_t* spd_cols, int64_t ld, int64_t i_base,
-                                           int64_t n, uint32_t key_off, uint8_t b[16]) {
-  const int g = (threadIdx.x >> 5) & 1;
-  if constexpr (QFULL) {
-    const __amdgpu_buffer_rsrc_t rs = make_rsrc(spd_cols + i_base * ld);
-    const uint32_t voff = (uint32_t)(16 * g) * (uint32_t)ld + key_off;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) b[r] = (uint8_t)buf_u8(rs, voff, (uint32_t)(r * ld));
-  } else {
-    // base at the clamped first row, so every offset below is >= 0
-    const int64_t ib = i_base < n ? i_base : n - 1;
-    const __amdgpu_buffer_rsrc_t rs = make_rsrc(spd_cols + ib * ld);
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      int64_t row = i_base + 16 * g + r;
-      row = row < n ? row : n - 1;
-      b[r] = (uint8_t)buf_u8(rs, (uint32_t)((row - ib) * ld) + key_off, 0u);
-    }
-  }
-}
 
 __device__ __forceinline__ int round_to_int(float x) {
   int r;
@@ -182,40 +193,27 @@ __device__ __forceinline__ void clamp_buckets(uint32_t (&w)[4]) {
     }
   }
 }
-template <int NB>
-__device__ __forceinline__ void clamp_buckets(uint8_t (&b)[16]) {
-  if constexpr (NB <= 128) {
-    uint32_t any = 0;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) any |= b[r];
-    if (__any((any & 0x80u) != 0)) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) b[r] = (b[r] & 0x80u) ? (uint8_t)0x7f : b[r];
-    }
-  }
-}
-
-// b: this lane's 16 bucket indices, as 16 bytes (gathered from spd columns)
-// or as 4 words (a 16-byte row segment of spd_t).
-// STAGE: b holds 16 bytes of the block's spd rows (lane l: row l / 2 of the
-// 32-query sub-block, bytes 16 (l % 2) .. + 15 of the wave's 32 keys); they
-// are written to the wave's staging buffer and each lane reads its key's 16
-// query bytes back with two 8-bit transposing reads (off_tr8).
-template <int D, int NKS, int NB, bool KTAIL, int BUF, int QS, bool STAGE = false, typename BT>
-__device__ __forceinline__ void dkdv_subblock(DkdvSmem<D, NB>& sm, const DkdvOffsets<D>& off,
+// Sub-block SUB of the query group's part of tile buffer BUF. w: kTrans: the
+// lane's 16 bucket indices (a 16-byte row segment of spd_t); else 16 bytes of
+// the block's spd rows (lane l: row l / 2 of the 32-query sub-block, bytes
+// 16 (l % 2) .. + 15 of the wave's 32 keys; kRowsAny: the 5 dwords that hold
+// them, at address sh mod 4), which are written to the wave's staging buffer,
+// where each lane reads its key's 16 query bytes back with two 8-bit
+// transposing reads (off_tr8). row0: the group's first row in a tile.
+template <int D, int NKS, int NB, bool KTAIL, int BUF, int SUB, SpdRead READ, int BQ, int NBT>
+__device__ __forceinline__ void dkdv_subblock(DkdvSmem<D, NB, BQ>& sm, const DkdvOffsets<D>& off,
                                               const bf16x8* kf, const bf16x8* vf,
-                                              const BT* b, float sl2, bool jok,
-                                              f32x16* dk, f32x16* dv, const int* off_tr8 = nullptr) {
-  constexpr int NKC = D / 16;
+                                              uint32_t (&b)[NBT], uint32_t sh, float sl2, bool jok, int row0,
+                                              f32x16* dk, f32x16* dv, const int* off_tr8) {
   constexpr int NCB = D / 32;
   const int lane = threadIdx.x & 63;
   const int g = lane >> 5;
-  const int ib = QS * 32 + 16 * g;   // this lane half's first query in the tile
+  const int ib = row0 + SUB * 32 + 16 * g;   // this lane half's first query in the tile
 
   f32x16 s, dp;
   {
-    const float4* is4 = reinterpret_cast<const float4*>(&sm.init_s[BUF][ib]);
-    const float4* ip4 = reinterpret_cast<const float4*>(&sm.init_p[BUF][ib]);
+    const float4* is4 = reinterpret_cast<const float4*>(&rows_of(sm).init_s[BUF][ib]);
+    const float4* ip4 = reinterpret_cast<const float4*>(&rows_of(sm).init_p[BUF][ib]);
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const float4 x = is4[u], y = ip4[u];
@@ -225,8 +223,8 @@ __device__ __forceinline__ void dkdv_subblock(DkdvSmem<D, NB>& sm, const DkdvOff
   }
 #pragma unroll
   for (int kc = 0; kc < NKS; ++kc) {
-    s = mfma32(lds_b128(sm.q[BUF] + QS * 32 * D + off.row[kc]), kf[kc], s);
-    dp = mfma32(lds_b128(sm.o[BUF] + QS * 32 * D + off.row[kc]), vf[kc], dp);
+    s = mfma32(lds_b128(sm.q[BUF] + SUB * 32 * D + off.row[kc]), kf[kc], s);
+    dp = mfma32(lds_b128(sm.o[BUF] + SUB * 32 * D + off.row[kc]), vf[kc], dp);
   }
   // Lane: key; registers r: queries. dp holds (dO.V - Dlt) 2^F, so ds below
   // is dS 2^F.
@@ -237,53 +235,35 @@ __device__ __forceinline__ void dkdv_subblock(DkdvSmem<D, NB>& sm, const DkdvOff
   // copy offset with the table base: kTabBase = 1 << 16 is byte 2, so a
   // byte permute can put the bucket into byte 1 and keep both
   const uint32_t cpyb = (uint32_t)(lane & (CPY - 1)) * 8u | kTabBase;
-  if constexpr (sizeof(BT) == 4) {
-    uint32_t w[4];
-    if constexpr (STAGE) {
-      typedef int i32x2 __attribute__((ext_vector_type(2)));
-      typedef __attribute__((address_space(3))) i32x2* lds_i32x2;
-      uint8_t* st8 = sm.stage[wave_id()];
-      uint4 v4 = make_uint4(b[0], b[1], b[2], b[3]);
-      opaque(v4);                                  // keep the load's wait here
-      *reinterpret_cast<uint4*>(st8 + 16 * lane) = v4;
+  uint32_t w[4];
+  if constexpr (READ != kTrans) {
+    typedef int i32x2 __attribute__((ext_vector_type(2)));
+    typedef __attribute__((address_space(3))) i32x2* lds_i32x2;
+    uint8_t* st8 = rows_of(sm).stage[wave_id()];
+    if constexpr (READ == kRowsAny) align_spd5(b, sh);
+    uint4 v4 = make_uint4(b[0], b[1], b[2], b[3]);
+    opaque(v4);                                  // keep the load's wait here
+    *reinterpret_cast<uint4*>(st8 + 16 * lane) = v4;
 #pragma unroll
-      for (int hh = 0; hh < 2; ++hh) {
-        const i32x2 v = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_i32x2)(void*)(st8 + off_tr8[hh]));
-        w[2 * hh] = (uint32_t)v.x;
-        w[2 * hh + 1] = (uint32_t)v.y;
-      }
-    } else {
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        w[u] = b[u];
-        opaque(w[u]);                              // keep the load's wait here
-      }
-    }
-    clamp_buckets<NB>(w);
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      if constexpr (CPY == 32)   // byte (r & 3) of w[r >> 2] times 256, plus copy and base
-        addr[r] = __builtin_amdgcn_perm(w[r >> 2], cpyb, 0x0c020000u | ((4u + (r & 3)) << 8));
-      else
-        addr[r] = (((w[r >> 2] >> (8 * (r & 3))) & 0xffu) << 7) | cpyb;
+    for (int hh = 0; hh < 2; ++hh) {
+      const i32x2 v = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_i32x2)(void*)(st8 + off_tr8[hh]));
+      w[2 * hh] = (uint32_t)v.x;
+      w[2 * hh + 1] = (uint32_t)v.y;
     }
   } else {
-    uint8_t bb[16];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      uint32_t bk = b[r];
-      opaque(bk);                                  // keep the byte's wait here
-      bb[r] = (uint8_t)bk;
+    for (int u = 0; u < 4; ++u) {
+      w[u] = b[u];
+      opaque(w[u]);                              // keep the load's wait here
     }
-    clamp_buckets<NB>(bb);
+  }
+  clamp_buckets<NB>(w);
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const uint32_t bk = bb[r];
-      if constexpr (CPY == 32)
-        addr[r] = __builtin_amdgcn_perm(bk, cpyb, 0x0c020400u);   // byte0(bk) * 256 + copy + base
-      else
-        addr[r] = (bk << 7) | cpyb;
-    }
+  for (int r = 0; r < 16; ++r) {
+    if constexpr (CPY == 32)   // byte (r & 3) of w[r >> 2] times 256, plus copy and base
+      addr[r] = __builtin_amdgcn_perm(w[r >> 2], cpyb, 0x0c020000u | ((4u + (r & 3)) << 8));
+    else
+      addr[r] = (((w[r >> 2] >> (8 * (r & 3))) & 0xffu) << 7) | cpyb;
   }
   const uint8_t* lds0 = reinterpret_cast<const uint8_t*>(&sm);
 #pragma unroll
@@ -298,7 +278,7 @@ __device__ __forceinline__ void dkdv_subblock(DkdvSmem<D, NB>& sm, const DkdvOff
     p[r] = pv;
     ds[r] = pv * dp[r];
   }
-  constexpr uint32_t kHistOff = DkdvSmem<D, NB>::ENT * 8;
+  constexpr uint32_t kHistOff = DkdvTable<NB>::ENT * 8;
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
     unsigned long long* hp = reinterpret_cast<unsigned long long*>(const_cast<uint8_t*>(lds0) + addr[r] + kHistOff);
@@ -311,20 +291,26 @@ __device__ __forceinline__ void dkdv_subblock(DkdvSmem<D, NB>& sm, const DkdvOff
     const bf16x8 db = cvt_bf16x8(ds + 8 * q);
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb) {
-      const int base = (QS * 32 + 8 * q) * D;
+      const int base = (SUB * 32 + 8 * q) * D;
       dv[cb] = mfma32(lds_tr_operand(sm.o[BUF] + base, off.tr[0][cb], off.tr[1][cb]), pb, dv[cb]);
       dk[cb] = mfma32(lds_tr_operand(sm.q[BUF] + base, off.tr[0][cb], off.tr[1][cb]), db, dk[cb]);
     }
   }
 }
 
-template <int D, int DS, int NB, bool KTAIL, bool QFULL, bool TR, bool STAGE>
-__device__ __forceinline__ void dkdv_main(const BwdArgs& a, DkdvSmem<D, NB>& sm, int h, int64_t key0,
+template <int D, int DS, int NB, int QS, bool KTAIL, SpdRead READ, int BQ>
+__device__ __forceinline__ void dkdv_main(const BwdArgs& a, DkdvSmem<D, NB, BQ>& sm, int h, int64_t key0,
                                           int64_t j, bool jok, int fexp) {
   constexpr int NKC = D / 16;
   constexpr int NCB = D / 32;
+  constexpr int NKW = kNW / QS;                // waves per query group
+  constexpr int NSUB = BQ / (32 * QS);         // 32-query sub-blocks per wave and tile
+  static_assert(NSUB == 1 || NSUB == 2, "one or two sub-blocks per wave and tile");
   const int lane = threadIdx.x & 63;
   const int g = lane >> 5;
+  const int qs = QS == 1 ? 0 : wave_id() / NKW;
+  const int kw = QS == 1 ? wave_id() : wave_id() % NKW;
+  const int row0 = qs * NSUB * 32;             // the group's first row in a tile
   const int64_t hq = (int64_t)h * a.Sq * DS;   // query-side rows
   const int64_t hk = (int64_t)h * a.Sk * DS;   // key-side rows
   const uint16_t* qh = reinterpret_cast<const uint16_t*>(a.q) + hq;
@@ -358,68 +344,86 @@ __device__ __forceinline__ void dkdv_main(const BwdArgs& a, DkdvSmem<D, NB>& sm,
 
   const int64_t ld = a.ld_spd;
   const int64_t jc = jok ? j : a.Sk - 1;
-  const uint32_t key_off = (uint32_t)(jc - key0);
   const uint8_t* spd_cols = seq_spd(a, h) + a.row_off * ld + a.col_off + key0;
-  const int64_t ntiles = (a.Sq + kBQ - 1) / kBQ;
-  const DkdvOffsets<D> off;
+  const int64_t ntiles = (a.Sq + BQ - 1) / BQ;
+  const DkdvOffsets<D> off(row0);
 
-  // Bucket indices of this lane's key: TR reads 16 queries as one 16-byte
-  // row segment of spd_t (rows of this key block only; past the block's last
-  // row a load reads zeros), else gathers 16 bytes of a spd column.
-  using BT = std::conditional_t<TR || STAGE, uint32_t, uint8_t>;
-  constexpr int NBT = TR || STAGE ? 4 : 16;
-  static_assert(!(TR && STAGE), "one way of reading spd");
+  // Bucket indices of this lane's key. kTrans: 16 queries as one 16-byte row
+  // segment of spd_t (rows of this key block only; past the block's last row
+  // a load reads zeros). Else lane l loads row l / 2 of the sub-block, bytes
+  // 16 (l % 2) .. + 15 of the wave's 32 keys, through a resource that starts
+  // at the sub-block's first row and ends with the last query row's last key
+  // (rows past Sq read zero, a sub-block past Sq reads the last one; their P is
+  // 0). The sub-block's first row is a multiple of 32, so the lane's address
+  // mod 16 is the same for every sub-block.
+  constexpr int BK = NKW * 32;
+  constexpr int NBT = READ == kRowsAny ? 5 : 4;
   const __amdgpu_buffer_rsrc_t rs_t =
-      make_rsrc_n(TR ? seq_spd_t(a, h) + key0 * ld : seq_spd(a, h), ((a.Sk - key0 < kBK ? a.Sk - key0 : kBK)) * ld);
-  const uint32_t voff_t = (uint32_t)((jc - key0) * ld) + 16u * (uint32_t)g;
-  // STAGE: lane l loads row l / 2 of the sub-block, bytes 16 (l % 2) .. + 15
-  // of the wave's 32 keys, through a resource that starts at the sub-block's
-  // first row and ends with the last query row (rows past Sq read zero); the
-  // two transposing reads of the staged block give the lane its key's 16
-  // query bytes.
-  uint32_t voff_st = 0;
+      make_rsrc_n(READ == kTrans ? seq_spd_t(a, h) + key0 * ld : seq_spd(a, h),
+                  (a.Sk - key0 < BK ? a.Sk - key0 : BK) * ld);
+  uint32_t voff = (uint32_t)((jc - key0) * ld) + 16u * (uint32_t)g;
+  uint32_t sh = 0;
   int off_tr8[2] = {0, 0};
-  if constexpr (STAGE) {
-    voff_st = (uint32_t)((lane >> 1) * ld) + (uint32_t)(wave_id() * 32 + 16 * (lane & 1));
+  if constexpr (READ != kTrans) {
+    voff = (uint32_t)((lane >> 1) * ld) + (uint32_t)(kw * 32 + 16 * (lane & 1));
+    if constexpr (READ == kRowsAny) {
+      voff += (uint32_t)(reinterpret_cast<uintptr_t>(spd_cols) & 15u);
+      sh = voff & 3u;
+      voff -= sh;
+    }
 #pragma unroll
     for (int hh = 0; hh < 2; ++hh)
       off_tr8[hh] = (16 * g + 8 * hh + ((lane & 15) >> 1)) * 32 + 16 * ((lane >> 4) & 1) + 8 * (lane & 1);
   }
-  auto fetch = [&](int64_t i_base, BT* dst) {
-    if constexpr (TR) {
-      buf_u128(rs_t, voff_t, (uint32_t)i_base, reinterpret_cast<uint32_t*>(dst));
-    } else if constexpr (STAGE) {
-      const int64_t ib = i_base < a.Sq ? i_base : a.Sq - 1;
-      const __amdgpu_buffer_rsrc_t rs = make_rsrc_n(spd_cols + ib * ld, (a.Sq - ib) * ld);
-      buf_u128(rs, voff_st + (uint32_t)((i_base - ib) * ld), 0u, reinterpret_cast<uint32_t*>(dst));
+  const int64_t last32 = (a.Sq - 1) & ~(int64_t)31;
+  auto fetch = [&](int64_t i_base, uint32_t (&dst)[NBT]) {
+    if constexpr (READ == kTrans) {
+      buf_u128(rs_t, voff, (uint32_t)i_base, dst);
     } else {
-      load_bytes<QFULL>(spd_cols, ld, i_base, a.Sq, key_off, reinterpret_cast<uint8_t*>(dst));
+      const int64_t ib = i_base < last32 ? i_base : last32;
+      uint32_t rem;
+      const __amdgpu_buffer_rsrc_t rs =
+          spd_rsrc<READ == kRowsAny>(spd_cols + ib * ld, (a.Sq - 1 - ib) * ld + (a.Sk - key0), rem);
+      if constexpr (READ == kRowsAny)
+        load_spd5(rs, voff, 0u, dst);
+      else
+        buf_u128(rs, voff, 0u, dst);
     }
   };
 
-  QTileStage<D, DS> st;
+  QTileStage<D, DS, BQ> st;
   st.load(qh, oh, lse2h, dlth, 0, a.Sq);
-  BT bA[NBT], bB[NBT];
-  fetch(0, bA);
+  uint32_t bA[NBT], bB[NBT];
+  fetch(row0, bA);
   st.template store<0>(sm, 0, a.Sq, inv_sl2, sF);
   wait_loads();
   __syncthreads();
 
   // One query tile on buffer BUF: the prefetches are unconditional (the last
   // tile re-reads itself), so every path has the same loads in flight and
-  // the waits before each use stay exact.
+  // the waits before each use stay exact. The words of one sub-block per tile
+  // sit in the set of the tile's buffer, those of two in bA, then bB.
+  constexpr int NKX = (DS + 15) / 16;
   auto step = [&](int64_t t, auto bufc) {
     constexpr int BUF = decltype(bufc)::value;
-    const int64_t i0 = t * kBQ;
+    const int64_t i0 = t * BQ;
     const bool more = t + 1 < ntiles;
-    const int64_t inext = more ? i0 + kBQ : i0;
-    fetch(i0 + 32, bB);
+    const int64_t inext = more ? i0 + BQ : i0;
+    if constexpr (NSUB == 2)
+      fetch(i0 + row0 + 32, bB);
+    else
+      fetch(inext + row0, BUF == 0 ? bB : bA);
     st.load(qh, oh, lse2h, dlth, inext, a.Sq);
     sched_fence();
-    dkdv_subblock<D, (DS + 15) / 16, NB, KTAIL, BUF, 0, STAGE>(sm, off, kf, vf, bA, sl2, jok, dk, dv, off_tr8);
-    fetch(inext, bA);
-    sched_fence();
-    dkdv_subblock<D, (DS + 15) / 16, NB, KTAIL, BUF, 1, STAGE>(sm, off, kf, vf, bB, sl2, jok, dk, dv, off_tr8);
+    if constexpr (NSUB == 2) {
+      dkdv_subblock<D, NKX, NB, KTAIL, BUF, 0, READ>(sm, off, kf, vf, bA, sh, sl2, jok, row0, dk, dv, off_tr8);
+      fetch(inext + row0, bA);
+      sched_fence();
+      dkdv_subblock<D, NKX, NB, KTAIL, BUF, 1, READ>(sm, off, kf, vf, bB, sh, sl2, jok, row0, dk, dv, off_tr8);
+    } else {
+      dkdv_subblock<D, NKX, NB, KTAIL, BUF, 0, READ>(sm, off, kf, vf, BUF == 0 ? bA : bB, sh, sl2, jok, row0, dk,
+                                                     dv, off_tr8);
+    }
     if (more) st.template store<BUF ^ 1>(sm, inext, a.Sq, inv_sl2, sF);
     __syncthreads();
   };
@@ -430,6 +434,41 @@ __device__ __forceinline__ void dkdv_main(const BwdArgs& a, DkdvSmem<D, NB>& sm,
   }
   if (t < ntiles) step(t, std::integral_constant<int, 0>());
 
+  if constexpr (QS > 1) {
+    // group qs + half's dK and dV are added to group qs's through the LDS
+    // below the table (the last step's barrier has ended every read of it)
+    constexpr int XW = 2 * NCB * 16 * 64;      // floats of one wave's accumulators
+    static_assert(XW * 4 * kNW / 2 <= (int)kTabBase, "the exchange fits below the table");
+    float* xbuf = reinterpret_cast<float*>(&sm);
+#pragma unroll
+    for (int half = QS / 2; half >= 1; half /= 2) {
+      if (qs >= half && qs < 2 * half) {
+        float4* x = reinterpret_cast<float4*>(xbuf + ((qs - half) * NKW + kw) * XW) + lane;
+#pragma unroll
+        for (int cb = 0; cb < NCB; ++cb)
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            x[(cb * 8 + u) * 64] = make_float4(dk[cb][4 * u], dk[cb][4 * u + 1], dk[cb][4 * u + 2], dk[cb][4 * u + 3]);
+            x[(cb * 8 + 4 + u) * 64] =
+                make_float4(dv[cb][4 * u], dv[cb][4 * u + 1], dv[cb][4 * u + 2], dv[cb][4 * u + 3]);
+          }
+      }
+      __syncthreads();
+      if (qs < half) {
+        const float4* x = reinterpret_cast<const float4*>(xbuf + (qs * NKW + kw) * XW) + lane;
+#pragma unroll
+        for (int cb = 0; cb < NCB; ++cb)
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const float4 y = x[(cb * 8 + u) * 64], z = x[(cb * 8 + 4 + u) * 64];
+            dk[cb][4 * u] += y.x; dk[cb][4 * u + 1] += y.y; dk[cb][4 * u + 2] += y.z; dk[cb][4 * u + 3] += y.w;
+            dv[cb][4 * u] += z.x; dv[cb][4 * u + 1] += z.y; dv[cb][4 * u + 2] += z.z; dv[cb][4 * u + 3] += z.w;
+          }
+      }
+      __syncthreads();
+    }
+    if (qs != 0) return;
+  }
   const float dk_scale = a.scale * ldexpf(1.0f, -fexp);
   if (jok && a.accumulate) {
     // fp32 partials of the key block, accumulated across ring steps
@@ -474,23 +513,25 @@ __device__ __forceinline__ void dkdv_main(const BwdArgs& a, DkdvSmem<D, NB>& sm,
 
 // D: the tile's head dim (32 or 64); DS <= D: the head dim of the tensors
 // (8 and 16 run on 32-wide tiles whose extra features are zero).
-template <int D, int DS, int NB, bool QFULL, bool TR, bool STAGE = false>
+template <int D, int DS, int NB, int QS, SpdRead READ>
 __global__ __launch_bounds__(kThreads, 2) void bwd_dkdv_bf16_kernel(BwdArgs a) {
   constexpr int CPY = copies<NB>();
-  __shared__ __attribute__((aligned(16))) DkdvSmem<D, NB> sm;
-  uint2* tabw = sm.tabw;
-  unsigned long long* hist = sm.hist;
-  float (*red)[kNW] = sm.red;
+  constexpr int kBK = kNW / QS * 32;           // keys per workgroup
+  using Smem = DkdvSmem<D, NB, dkdv_tile_rows<D, QS>()>;
+  __shared__ __attribute__((aligned(16))) Smem sm;
+  uint2* tabw = sm.t.tabw;
+  unsigned long long* hist = sm.t.hist;
+  float (*red)[kNW] = rows_of(sm).red;
   const int tid = threadIdx.x;
   const int wave = wave_id(), col = tid & 31;
   const int64_t nkb = (a.Sk + kBK - 1) / kBK;
   const int64_t lid = xcd_remap(blockIdx.x, nkb * a.H);
   const int h = (int)(lid % a.H);
   const int64_t kblk = lid / a.H;
-  const int64_t j = kblk * kBK + wave * 32 + col;
+  const int64_t j = kblk * kBK + (QS == 1 ? wave : wave % (kNW / QS)) * 32 + col;
   const bool jok = j < a.Sk;
 
-  for (int t = tid; t < DkdvSmem<D, NB>::ENT; t += kThreads) {
+  for (int t = tid; t < DkdvTable<NB>::ENT; t += kThreads) {
     const int bkt = t / CPY;
     const float tv = (bkt < a.n_buckets) ? a.table[(int64_t)table_row(a, h) * a.n_buckets + bkt] * kLog2e : 0.0f;
     tabw[t] = make_uint2(__float_as_uint(tv), 0u);
@@ -538,9 +579,9 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dkdv_bf16_kernel(BwdArgs a) {
   }
 
   if ((kblk + 1) * kBK <= a.Sk)
-    dkdv_main<D, DS, NB, false, QFULL, TR, STAGE>(a, sm, h, kblk * kBK, j, jok, fexp);
+    dkdv_main<D, DS, NB, QS, false, READ>(a, sm, h, kblk * kBK, j, jok, fexp);
   else
-    dkdv_main<D, DS, NB, true, QFULL, TR, STAGE>(a, sm, h, kblk * kBK, j, jok, fexp);
+    dkdv_main<D, DS, NB, QS, true, READ>(a, sm, h, kblk * kBK, j, jok, fexp);
 
   __syncthreads();
   const double unscale = ldexp(1.0, -fexp);
@@ -552,24 +593,26 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dkdv_bf16_kernel(BwdArgs a) {
   }
 }
 
+template <int D, int DS, int NB, int QS>
+void launch_dkdv_qs(const BwdArgs& a, hipStream_t s) {
+  constexpr int BK = kNW / QS * 32;
+  const dim3 grid((unsigned)((a.Sk + BK - 1) / BK * a.H));
+  if (a.spd_t)
+    hipLaunchKernelGGL((bwd_dkdv_bf16_kernel<D, DS, NB, QS, kTrans>), grid, dim3(kThreads), 0, s, a);
+  else if (a.spd_dw)
+    hipLaunchKernelGGL((bwd_dkdv_bf16_kernel<D, DS, NB, QS, kRowsDw>), grid, dim3(kThreads), 0, s, a);
+  else
+    hipLaunchKernelGGL((bwd_dkdv_bf16_kernel<D, DS, NB, QS, kRowsAny>), grid, dim3(kThreads), 0, s, a);
+}
+
 template <int D, int DS, int NB>
 void launch_dkdv_t(const BwdArgs& a, hipStream_t s) {
-  const int64_t nkb = (a.Sk + kBK - 1) / kBK;
-  const dim3 grid((unsigned)(nkb * a.H));
-  const bool qfull = a.Sq % kBQ == 0;
-  if (a.spd_t) {
-    if (qfull)
-      hipLaunchKernelGGL((bwd_dkdv_bf16_kernel<D, DS, NB, true, true>), grid, dim3(kThreads), 0, s, a);
-    else
-      hipLaunchKernelGGL((bwd_dkdv_bf16_kernel<D, DS, NB, false, true>), grid, dim3(kThreads), 0, s, a);
-  } else if (a.spd_vec) {
-    // rows 16-byte aligned: row-wise loads staged through LDS
-    hipLaunchKernelGGL((bwd_dkdv_bf16_kernel<D, DS, NB, true, false, true>), grid, dim3(kThreads), 0, s, a);
-  } else {
-    if (qfull)
-      hipLaunchKernelGGL((bwd_dkdv_bf16_kernel<D, DS, NB, true, false>), grid, dim3(kThreads), 0, s, a);
-    else
-      hipLaunchKernelGGL((bwd_dkdv_bf16_kernel<D, DS, NB, false, false>), grid, dim3(kThreads), 0, s, a);
+  const int qs = pick_split(a.Sk, a.Sq, a.H, kNW * 32, dkdv_tile_rows<D, 1>(), dkdv_tile_rows<D, 2>(),
+                            dkdv_tile_rows<D, 4>());
+  switch (qs) {
+    case 1: launch_dkdv_qs<D, DS, NB, 1>(a, s); break;
+    case 2: launch_dkdv_qs<D, DS, NB, 2>(a, s); break;
+    default: launch_dkdv_qs<D, DS, NB, 4>(a, s); break;
   }
 }
 

@@ -223,7 +223,8 @@ __global__ __launch_bounds__(kThreads, 1) void bwd_dq_bf16_kernel(BwdArgs a) {
   const int64_t ld = a.ld_spd;
   const int64_t rb = qbase < a.Sq ? qbase : a.Sq - 1;
   using Spd = SpdStream<ROWS, TR>;
-  const Spd spd(seq_spd(a, h) + (a.row_off + rb) * ld + a.col_off, a.Sk, ks * kOff, g);
+  const Spd spd(seq_spd(a, h) + (a.row_off + rb) * ld + a.col_off, (a.Sq - 1 - rb) * ld + a.Sk, a.Sk,
+                ks * kOff, g);
   const typename Spd::Row srow = spd.row((qrow - rb) * ld);
   const int64_t ntiles = spd.ntiles;
 
@@ -259,16 +260,10 @@ __global__ __launch_bounds__(kThreads, 1) void bwd_dq_bf16_kernel(BwdArgs a) {
     for (int p = 0; p < 2; ++p)
 #pragma unroll
       for (int kb = 0; kb < KB; ++kb) spd.fetch(p, srow, kb, w[p][kb]);
-    if (spd.tiny()) {
-      const uint8_t* row = seq_spd(a, h) + (a.row_off + qrow) * ld + a.col_off;
-#pragma unroll
-      for (int kb = 0; kb < KB; ++kb)
-        load_spd16_bytes(row, ks * kOff + kb * 32 + 16 * g, a.Sk, w[0][kb]);
-    }
     wait_vmcnt<0>();
     __syncthreads();     // table, tiles 0..2
     if (active) {
-      spd.ready(0, RAG, srow, 0, w[0][0]);
+      spd.ready(srow, w[0][0]);
       issue_block<D, NKS>(sTab, w[0][0], lane4, sK0 + goff, sV0 + goff, off, 0, ln, s0, dp0);
     }
   }
@@ -299,7 +294,7 @@ __global__ __launch_bounds__(kThreads, 1) void bwd_dq_bf16_kernel(BwdArgs a) {
     auto& wn = w[decltype(setc)::value ^ 1];
     if constexpr (KB == 2) {
       read_kt<D>(k_s, off, 0, kt);
-      spd.ready(t, END, srow, 1, wt[1]);
+      spd.ready(srow, wt[1]);
       block_dq<D, NKS, END>(sTab, wt[1], lane4, k_s, v_s, off, 1, ln, s1, dp1, s0, dp0, kt, jrem, sl2, acc);
       read_kt<D>(k_s, off, 1, kt);
     } else {
@@ -315,14 +310,12 @@ __global__ __launch_bounds__(kThreads, 1) void bwd_dq_bf16_kernel(BwdArgs a) {
     __builtin_amdgcn_s_barrier();
     copy_tile(t + 3, stagec);
     sched_fence();
-    spd.ready(t + 1, END, srow, 0, wn[0]);
+    spd.ready(srow, wn[0]);
     block_dq<D, NKS, END>(sTab, wn[0], lane4, k_n + goff, v_n + goff, off, 0, ln, s0, dp0, s1, dp1, kt,
                           jrem - (KB - 1) * 32, sl2, acc);
   };
   {
-    // the step before the last tile is an END step too: it makes that tile's
-    // first words ready
-    const int64_t nmain = RAG ? ntiles - 2 : ntiles;
+    const int64_t nmain = RAG ? ntiles - 1 : ntiles;
     int64_t t = 0;
     for (; t + 6 <= nmain; t += 6) {
       step(t, S0(), P0(), Main());
@@ -339,7 +332,6 @@ __global__ __launch_bounds__(kThreads, 1) void bwd_dq_bf16_kernel(BwdArgs a) {
     if (t + 4 < ntiles) step(t + 4, S1(), P0(), End());
     if constexpr (RAG) {
       if (t + 5 < ntiles) step(t + 5, S2(), P1(), End());
-      if (t + 6 < ntiles) step(t + 6, S0(), P0(), End());
     }
   }
   wait_vmcnt<0>();     // drain the clamped copies issued past the last tile
@@ -429,7 +421,7 @@ void launch_dq_ks(const BwdArgs& a, hipStream_t s) {
 
 template <int D, int DS>
 void launch_dq_t(const BwdArgs& a, hipStream_t s) {
-  switch (pick_split(a.Sq, a.Sk, a.H, kWaves * 32, D == 64 ? 128 : 256, 4)) {
+  switch (pick_split(a.Sq, a.Sk, a.H, kWaves * 32, split_tile_rows<D, 1>(), split_tile_rows<D, 2>(), split_tile_rows<D, 4>())) {
     case 1: launch_dq_ks<D, DS, 1>(a, s); break;
     case 2: launch_dq_ks<D, DS, 2>(a, s); break;
     default: launch_dq_ks<D, DS, 4>(a, s); break;

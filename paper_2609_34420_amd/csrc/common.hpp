@@ -161,52 +161,21 @@ __device__ __forceinline__ void buf_u128(__amdgpu_buffer_rsrc_t r, uint32_t voff
   w[0] = v[0]; w[1] = v[1]; w[2] = v[2]; w[3] = v[3];
 }
 
-// spd rows from p on, any byte alignment: a resource whose base is 16-byte
-// aligned and the bytes from it to p (to be added to the lane offset).
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t spd_rsrc(const uint8_t* p, uint32_t& rem) {
-  rem = (uint32_t)(reinterpret_cast<uintptr_t>(p) & 15u);
-  return make_rsrc(p - rem);
-}
-
-// A 16-byte spd group at any byte address, as the 5 dwords that hold it: a
-// load of 16 bytes from an odd address costs up to 1.4 times the whole
-// forward (N = 16001 against 16004 at H = 8, d = 64: 936 and 659 us), one
-// from a dword boundary costs no more than an aligned one. The first form is
-// for groups that are followed by at least one more byte of spd; the second
-// never reads a dword that holds no byte of the group.
+// A 16-byte spd group at any byte address, as the 5 dwords that hold it (voff4
+// + soff: its address rounded down to a dword; dwords past the resource's end
+// read 0). A load of 16 bytes from an odd address costs up to 1.4 times the
+// whole forward (N = 16001 against 16004 at H = 8, d = 64: 936 and 659 us),
+// one from a dword boundary costs no more than an aligned one.
 __device__ __forceinline__ void load_spd5(__amdgpu_buffer_rsrc_t r, uint32_t voff4, uint32_t soff,
                                           uint32_t (&w)[5]) {
   const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, voff4, soff, 0);
   w[0] = v[0]; w[1] = v[1]; w[2] = v[2]; w[3] = v[3];
   w[4] = __builtin_amdgcn_raw_buffer_load_b32(r, voff4, soff + 16u, 0);
 }
-__device__ __forceinline__ void load_spd5_end(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t (&w)[5]) {
-  const uint32_t v4 = voff & ~3u;
-  const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, v4, 0, 0);
-  w[0] = v[0]; w[1] = v[1]; w[2] = v[2]; w[3] = v[3];
-  w[4] = __builtin_amdgcn_raw_buffer_load_b32(r, v4 + ((voff & 3u) ? 16u : 12u), 0, 0);
-}
 // Its 16 bytes into w[0..3] (sh: its address mod 4).
 __device__ __forceinline__ void align_spd5(uint32_t (&w)[5], uint32_t sh) {
 #pragma unroll
   for (int i = 0; i < 4; ++i) w[i] = __builtin_amdgcn_alignbyte(w[i + 1], w[i], sh);
-}
-
-// Drops the first n bytes (0..15) of the 16 in w and appends zeros: a group
-// that ends past its row is loaded as the row's last 16 bytes instead, so no
-// load leaves the row, and moved into place with this.
-template <int NW>
-__device__ __forceinline__ void shift_spd16(uint32_t (&w)[NW], int n) {
-  uint64_t lo = (uint64_t)w[0] | ((uint64_t)w[1] << 32), hi = (uint64_t)w[2] | ((uint64_t)w[3] << 32);
-  if (n >= 8) {
-    lo = hi;
-    hi = 0;
-  }
-  const int b = 8 * (n & 7);
-  lo = (lo >> b) | ((hi << 1) << (63 - b));
-  hi >>= b;
-  w[0] = (uint32_t)lo; w[1] = (uint32_t)(lo >> 32);
-  w[2] = (uint32_t)hi; w[3] = (uint32_t)(hi >> 32);
 }
 
 // 16 spd bytes row[j .. j+15] as four dwords, byte by byte, bytes at or past

@@ -129,13 +129,13 @@ __global__ __launch_bounds__(128) void fwd_valu_kernel(FwdArgs a) {
 // workgroup, in units of one tile step of 2 blocks per wave (1.2-1.3 us in the
 // d = 64 forward; a step of one block measured 0.55 of it, setting a workgroup
 // up and finishing it about three steps).
-int pick_split(int64_t rows, int64_t cols, int64_t heads, int rows1, int max_tile, int max_split) {
+int pick_split(int64_t rows, int64_t cols, int64_t heads, int rows1, int tile1, int tile2, int tile4) {
   int best = 1;
   double best_cost = 0.0;
-  for (int ks = 1; ks <= max_split; ks *= 2) {
+  for (int ks = 1; ks <= 4; ks *= 2) {
     const int64_t wgs = (rows + rows1 / ks - 1) / (rows1 / ks) * heads;
     const int64_t rounds = (wgs + 255) / 256;
-    const int tile = 64 * ks < max_tile ? 64 * ks : max_tile;
+    const int tile = ks == 1 ? tile1 : (ks == 2 ? tile2 : tile4);
     const double step = tile / (32 * ks) == 2 ? 1.0 : 0.55;
     const double cost = (double)rounds * ((double)((cols + tile - 1) / tile) * step + 3.0);
     if (ks == 1 || cost < best_cost) {
@@ -147,7 +147,7 @@ int pick_split(int64_t rows, int64_t cols, int64_t heads, int rows1, int max_til
 }
 
 int fwd_key_split(const FwdArgs& a, int D) {
-  return pick_split(a.Sq, a.Sk, a.H, 512, D == 64 ? 128 : 256, 4);
+  return pick_split(a.Sq, a.Sk, a.H, 512, 64, 128, D == 64 ? 128 : 256);
 }
 
 hipError_t launch_fwd(const FwdArgs& a, int d, bool bf16, bool out_f32, hipStream_t s) {

@@ -131,7 +131,8 @@ __global__ __launch_bounds__(kThreads, 1) void fwd_bf16_kernel(FwdArgs a) {
   const int64_t ld = a.ld_spd;
   const int64_t rb = qbase < a.Sq ? qbase : a.Sq - 1;
   using Spd = SpdStream<ROWS, TR>;
-  const Spd spd(seq_spd(a, h) + (a.row_off + rb) * ld + a.col_off, a.Sk, ks * kOff, g);
+  const Spd spd(seq_spd(a, h) + (a.row_off + rb) * ld + a.col_off, (a.Sq - 1 - rb) * ld + a.Sk, a.Sk,
+                ks * kOff, g);
   typename Spd::Row srow[kQB];
 #pragma unroll
   for (int qb = 0; qb < kQB; ++qb) srow[qb] = spd.row((qrow[qb] - rb) * ld);
@@ -177,9 +178,9 @@ __global__ __launch_bounds__(kThreads, 1) void fwd_bf16_kernel(FwdArgs a) {
   constexpr int NS = Spd::BYTES && D == 64 && KB == 2 ? 1 : 2;
   uint32_t w[NS][kQB][KB][Spd::NWD];
   // Score product of unit (kb, qb) of tile tt (set P) from staged keys k_t.
-  auto scores = [&](int64_t tt, auto setc, auto endc, int qb, int kb, const uint16_t* k_t, f32x16& s) {
+  auto scores = [&](int64_t tt, auto setc, int qb, int kb, const uint16_t* k_t, f32x16& s) {
     auto& wu = w[decltype(setc)::value % NS][qb][kb];
-    spd.ready(tt, decltype(endc)::value, srow[qb], kb, wu);
+    spd.ready(srow[qb], wu);
     issue_scores<D, NKS>(sTab, wu, lane4, k_t, off.k, kb, qf[qb], s);
     if constexpr (NS == 1) spd.fetch(tt + 1, srow[qb], kb, wu);
   };
@@ -198,18 +199,9 @@ __global__ __launch_bounds__(kThreads, 1) void fwd_bf16_kernel(FwdArgs a) {
       for (int qb = 0; qb < kQB; ++qb)
 #pragma unroll
         for (int kb = 0; kb < KB; ++kb) spd.fetch(p, srow[qb], kb, w[p][qb][kb]);
-    if (spd.tiny()) {
-#pragma unroll
-      for (int qb = 0; qb < kQB; ++qb) {
-        const uint8_t* row = seq_spd(a, h) + (a.row_off + qrow[qb]) * ld + a.col_off;
-#pragma unroll
-        for (int kb = 0; kb < KB; ++kb)
-          load_spd16_bytes(row, ks * kOff + kb * 32 + 16 * g, a.Sk, w[0][qb][kb]);
-      }
-    }
     wait_vmcnt<0>();
     __syncthreads();     // table, and tiles 0..2
-    if (active) scores(0, P0(), End(), 0, 0, sK0 + goff, s0);
+    if (active) scores(0, P0(), 0, 0, sK0 + goff, s0);
   }
   // Tile t from stage S = t % 3 and spd set t % NS; units u = (key block, query block) in the
   // order (0,0), (0,1), (1,0), (1,1). The score product of unit u + 1 is
@@ -245,13 +237,13 @@ __global__ __launch_bounds__(kThreads, 1) void fwd_bf16_kernel(FwdArgs a) {
     const int jrem = END ? (int)(a.Sk - t * TR) - ks * kOff : 0;
     bf16x8 vop[2][NCB];
     f32x16 s1, s2, s3;
-    scores(t, setc, endc, 1, 0, k_s, s1);
+    scores(t, setc, 1, 0, k_s, s1);
     read_v<D>(v_s, off, 0, vop);
     if constexpr (KB == 2) {
       softmax_pv<D, END>(s0, vop, jrem, sl2, sm[0], acc[0]);
-      scores(t, setc, endc, 0, 1, k_s, s2);
+      scores(t, setc, 0, 1, k_s, s2);
       softmax_pv<D, END>(s1, vop, jrem, sl2, sm[1], acc[1]);
-      scores(t, setc, endc, 1, 1, k_s, s3);
+      scores(t, setc, 1, 1, k_s, s3);
       read_v<D>(v_s, off, 1, vop);
       fetch2();
       sched_fence();
@@ -268,16 +260,14 @@ __global__ __launch_bounds__(kThreads, 1) void fwd_bf16_kernel(FwdArgs a) {
     __builtin_amdgcn_s_barrier();
     copy_tile(t + 3, stagec);
     sched_fence();
-    scores(t + 1, std::integral_constant<int, decltype(setc)::value ^ 1>(), endc, 0, 0, k_n + goff, s0);
+    scores(t + 1, std::integral_constant<int, decltype(setc)::value ^ 1>(), 0, 0, k_n + goff, s0);
     if constexpr (KB == 2)
       softmax_pv<D, END>(s3, vop, jrem - 32, sl2, sm[1], acc[1]);
     else
       softmax_pv<D, END>(s1, vop, jrem, sl2, sm[1], acc[1]);
   };
   {
-    // the step before the last tile is an END step too: it makes that tile's
-    // first words ready
-    const int64_t nmain = RAG ? ntiles - 2 : ntiles;
+    const int64_t nmain = RAG ? ntiles - 1 : ntiles;
     int64_t t = 0;
     for (; t + 6 <= nmain; t += 6) {
       step(t, S0(), P0(), Main());
@@ -294,7 +284,6 @@ __global__ __launch_bounds__(kThreads, 1) void fwd_bf16_kernel(FwdArgs a) {
     if (t + 4 < ntiles) step(t + 4, S1(), P0(), End());
     if constexpr (RAG) {
       if (t + 5 < ntiles) step(t + 5, S2(), P1(), End());
-      if (t + 6 < ntiles) step(t + 6, S0(), P0(), End());
     }
   }
   wait_vmcnt<0>();     // drain the clamped copies issued past the last tile

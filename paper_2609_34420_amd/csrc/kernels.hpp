@@ -41,7 +41,7 @@ struct BwdArgs {
   const void* k;
   const void* v;
   const uint8_t* spd;     // (query i, key j) at spd[(row_off + i) * ld_spd + col_off + j]
-  const uint8_t* spd_t;   // transpose of spd (same ld, zero offsets), or null: gather columns
+  const uint8_t* spd_t;   // transpose of spd (same ld, zero offsets), or null: read spd by rows
   int64_t ld_spd;
   int64_t row_off;
   int64_t col_off;
@@ -99,9 +99,9 @@ hipError_t launch_fwd(const FwdArgs& a, int d, bool bf16, bool out_f32, hipStrea
 template <int D, int DS, bool OUT_F32>
 hipError_t launch_fwd_mfma(const FwdArgs& a, hipStream_t s);
 int fwd_key_split(const FwdArgs& a, int D);
-// The split ks = 1, 2, .. max_split that finishes first, for workgroups of
-// rows1 / ks rows over tiles of min(64 ks, max_tile) columns.
-int pick_split(int64_t rows, int64_t cols, int64_t heads, int rows1, int max_tile, int max_split);
+// The split ks = 1, 2 or 4 that finishes first, for workgroups of rows1 / ks
+// rows over tiles of tile1, tile2, tile4 columns.
+int pick_split(int64_t rows, int64_t cols, int64_t heads, int rows1, int tile1, int tile2, int tile4);
 // Sequences of at most 256 rows, N a multiple of 4 (bf16 in and out,
 // d <= 32, at most 127 buckets, spd rows 4-byte aligned): the persistent
 // whole-sequence forward.

@@ -71,10 +71,10 @@ __device__ __forceinline__ uint32_t src_chunk_off(int row, int chunk) {
 // tile of them is contiguous in global memory) and the chunks past DS read
 // as zero. With fewer items than threads, the extra threads load a
 // duplicate (so every wave issues the same loads) and store nothing.
-template <int D, int NT, int DS = D>
+template <int D, int NT, int DS = D, int ROWS = kTileRows>
 struct RowStage {
   static constexpr int CPR = D / 8;
-  static constexpr int ITEMS = kTileRows * CPR;
+  static constexpr int ITEMS = ROWS * CPR;
   static constexpr int IPT = ITEMS >= NT ? ITEMS / NT : 1;
   static_assert(ITEMS % NT == 0 || NT % ITEMS == 0, "tile items must divide evenly");
   uint4 r[IPT];
@@ -241,77 +241,65 @@ __device__ __forceinline__ void load_bias(const float* tab, const uint32_t (&w)[
   }
 }
 
+// Resource over `bytes` spd bytes from p on, rounded up to the end of the last
+// byte's dword: reads through it never touch a dword that holds no byte of
+// them (past the end they return 0, dword by dword). ANY: p may be any
+// address; the resource then starts at the 16-byte boundary below it and rem
+// is the distance to p. Otherwise p is on a dword boundary.
+template <bool ANY>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t spd_rsrc(const uint8_t* p, int64_t bytes, uint32_t& rem) {
+  rem = ANY ? (uint32_t)(reinterpret_cast<uintptr_t>(p) & 15u) : 0u;
+  return make_rsrc_n(p - rem, (bytes + rem + 3) & ~(int64_t)3);
+}
+
 // Sizes and spd alignment a query-stationary kernel takes. kWhole: the query
 // rows a multiple of the workgroup's, Sk of the tile, spd rows on dword
-// boundaries. kRagged: any sizes, spd rows on dword boundaries; in the last
-// tile, a group of 16 spd bytes that would end past the row's last key is
-// loaded as the row's last 16 bytes and shifted into place, and the scores
-// past the last key are masked. kBytes: any sizes and any spd address; each
-// group is loaded as the 5 dwords that hold it and aligned when its scores
-// come up.
+// boundaries. kRagged: any sizes, spd rows on dword boundaries; the scores past
+// the last key are masked (their spd bytes are the next row's, or 0 past the
+// end). kBytes: any sizes and any spd address; each group of 16 spd bytes is
+// loaded as the 5 dwords that hold it and aligned when its scores come up.
 enum SpdRows { kWhole = 0, kRagged = 1, kBytes = 2 };
 
 // The spd words a wave of a query-stationary kernel streams: for the lane's
 // query rows, groups of 16 keys (lane half g: keys 16 g .. + 15 of each 32-key
-// block kb < KB) of the wave's part (from key `part` on) of every TR-key tile,
-// by raw buffer loads: scalar base per wave, lane offset row * ld + 16 g,
-// scalar key offset.
+// block kb) of the wave's part (from key `part` on) of every TR-key tile, by
+// raw buffer loads: scalar base per wave, lane offset row * ld + 16 g, scalar
+// key offset.
 template <SpdRows ROWS, int TR>
 struct SpdStream {
-  static constexpr bool RAG = ROWS != kWhole, BYTES = ROWS == kBytes;
+  static constexpr bool BYTES = ROWS == kBytes;
   static constexpr int NWD = BYTES ? 5 : 4;          // dwords of a group in flight
   static constexpr int OPS = BYTES ? 2 : 1;          // vector-memory ops per group
   struct Row { uint32_t voff, sh; };                 // a lane's row: offset, its address mod 4 (kBytes)
 
-  uint32_t rem = 0;                                  // kBytes: bytes from the resource's base to row0
+  uint32_t rem = 0;
   __amdgpu_buffer_rsrc_t rs;
   int64_t ntiles;
-  int part, g16, nkeys, klast, jend;
+  int part, g16;
 
-  // row0: spd of the wave's first row and the block's first key.
-  __device__ __forceinline__ SpdStream(const uint8_t* row0, int64_t Sk, int part_, int g)
-      : rs(BYTES ? spd_rsrc(row0, rem) : make_rsrc(row0)), ntiles((Sk + TR - 1) / TR), part(part_), g16(16 * g),
-        nkeys((int)Sk), klast((int)Sk - 16), jend((int)((ntiles - 1) * TR) + part_ + 16 * g) {}
+  // row0: spd of the wave's first row and the block's first key; bytes: from
+  // there to the last query row's last key.
+  __device__ __forceinline__ SpdStream(const uint8_t* row0, int64_t bytes, int64_t Sk, int part_, int g)
+      : rs(ROWS == kWhole ? make_rsrc(row0) : spd_rsrc<BYTES>(row0, bytes, rem)), ntiles((Sk + TR - 1) / TR),
+        part(part_), g16(16 * g) {}
   __device__ __forceinline__ Row row(int64_t bytes) const {    // bytes: from the wave's first row
     Row r;
-    r.voff = (uint32_t)bytes + (uint32_t)g16 + (BYTES ? rem : 0u);
+    r.voff = (uint32_t)bytes + (uint32_t)g16 + rem;
     r.sh = BYTES ? r.voff & 3u : 0u;
     r.voff -= r.sh;
     return r;
   }
-  // Fewer than 16 keys: the caller loads them once, by bytes.
-  __device__ __forceinline__ bool tiny() const { return RAG && klast < 0; }
-  // Offset (from column 16 g) that group kb of the last tile is loaded from.
-  __device__ __forceinline__ int end_off(int kb) const {
-    return (jend + kb * 32 < klast ? jend + kb * 32 : klast) - g16;
-  }
   // Words of group kb of tile tt (clamped to the last).
   __device__ __forceinline__ void fetch(int64_t tt, const Row& r, int kb, uint32_t (&w)[NWD]) const {
     const int jt = (int)((tt < ntiles ? tt : ntiles - 1) * TR) + part + kb * 32;
-    if (tiny()) return;
-    if constexpr (BYTES) {
-      if (tt + 1 < ntiles)
-        load_spd5(rs, r.voff, (uint32_t)jt, w);
-      else
-        load_spd5_end(rs, r.voff + r.sh + (uint32_t)end_off(kb), w);
-    } else if constexpr (RAG) {
-      const int j = jt < klast - g16 ? jt : klast - g16;
-      buf_u128(rs, r.voff + (uint32_t)j, 0u, w);
-    } else {
+    if constexpr (BYTES)
+      load_spd5(rs, r.voff, (uint32_t)jt, w);
+    else
       buf_u128(rs, r.voff, (uint32_t)jt, w);
-    }
   }
-  // Its words moved into w[0..3] (bytes past the last key are masked by the
-  // caller). end: tt may be the last tile.
-  __device__ __forceinline__ void ready(int64_t tt, bool end, const Row& r, int kb, uint32_t (&w)[NWD]) const {
-    if (RAG && end && tt + 1 >= ntiles) {
-      if (tiny()) return;
-      const int j = jend + kb * 32;
-      if constexpr (BYTES) align_spd5(w, (r.sh + (uint32_t)end_off(kb)) & 3u);
-      shift_spd16(w, j > klast && j < nkeys ? j - klast : 0);
-    } else if constexpr (BYTES) {
-      align_spd5(w, r.sh);
-    }
+  // Its words moved into w[0..3].
+  __device__ __forceinline__ void ready(const Row& r, uint32_t (&w)[NWD]) const {
+    if constexpr (BYTES) align_spd5(w, r.sh);
   }
 };
 

@@ -125,40 +125,29 @@ def test_histogram_fixed_point_range():
     assert terms * 2 ** 30 < 2 ** 63
 
 
-@pytest.mark.parametrize("Sk", [16, 17, 31, 64, 100, 127, 130])
+@pytest.mark.parametrize("Sk", [1, 3, 16, 17, 31, 64, 100, 127, 130])
 @pytest.mark.parametrize("addr", [0, 1, 2, 3, 5, 14, 15])
 def test_spd_groups_at_any_address(Sk, addr):
-    """Forward and dQ: the group of 16 keys from key j of a row at byte `addr`
-    of a buffer that ends with the row. Every group but the row's last ones
-    is loaded as 16 bytes (dword-aligned rows) or as the 5 dwords that hold
-    it, shifted by its address mod 4; in the last tile the group starts at
-    min(j, Sk - 16), its fifth dword is read only if it holds a byte of the
-    group, and the group is moved down by j - (Sk - 16) bytes. Every key's
-    byte arrives in place and no dword without a byte of the row is read."""
+    """Forward, dQ and dK/dV: the group of 16 keys from key j of a buffer's
+    last row, which starts at byte `addr` past a 16-byte boundary and ends the
+    buffer. The resource starts at the boundary and ends with the dword of the
+    last key; dwords past its end read 0. Rows on dword boundaries are loaded
+    as 4 dwords; others as the 5 dwords from the address rounded down, shifted
+    by the address mod 4. Every key's byte arrives in place, and no dword is
+    read that holds no byte from the boundary on to the last key."""
     row = [(7 * j + 3) % 251 + 1 for j in range(Sk)]
-    buf = [0] * addr + row
-    end4 = (len(buf) + 3) // 4 * 4             # the last byte's dword
-    buf += [0xEE] * (end4 - len(buf))
+    end4 = (addr + Sk + 3) & ~3                # num_records of the resource
+    assert end4 - (addr + Sk) < 4
+    buf = [0xEE] * addr + row + [0xEE] * (end4 - addr - Sk)
 
     def dwords(a, n):
-        assert a % 4 == 0 and 0 <= a and a + 4 * n <= end4, (a, n)
-        return buf[a:a + 4 * n]
+        assert a % 4 == 0 and a >= 0
+        return sum((buf[x:x + 4] if x + 4 <= end4 else [0] * 4 for x in range(a, a + 4 * n, 4)), [])
 
-    tile = 64
-    for t in range((Sk + tile - 1) // tile):
-        last = (t + 1) * tile >= Sk
-        for j in range(t * tile, t * tile + tile, 16):
-            if last:
-                a = addr + min(j, Sk - 16)
-                w = dwords(a & ~3, 4) + dwords((a & ~3) + (16 if a & 3 else 12), 1)
-            else:
-                a = addr + j
-                w = dwords(a & ~3, 5)
-            w = w[a & 3:(a & 3) + 16]          # v_alignbyte over the 5 dwords
-            drop = j - (Sk - 16) if last and Sk - 16 < j < Sk else 0
-            assert 0 <= drop < 16
-            w = w[drop:] + [0] * drop
-            n = max(0, min(16, Sk - j))
-            assert w[:n] == row[j:j + n]
-            if a % 4 == 0 and not last:        # the aligned kernels' single load
-                assert dwords(a, 4)[:n] == row[j:j + n]
+    for j in range(0, (Sk + 63) // 64 * 64, 16):
+        a = addr + j
+        w = dwords(a & ~3, 5)[a & 3:(a & 3) + 16]   # v_alignbyte over the 5 dwords
+        n = max(0, min(16, Sk - j))
+        assert w[:n] == row[j:j + n]
+        if addr % 4 == 0:
+            assert dwords(a, 4)[:n] == row[j:j + n]
