@@ -19,8 +19,8 @@ PKG = Path(__file__).resolve().parent
 CSRC = PKG / "csrc"
 LIB = PKG / "libgtattn.so"
 BUILD_DIR = PKG / "_build"
-SOURCES = ["api.hip", "fwd.hip", "fwd_d64.hip", "fwd_d32.hip", "fwd_d16.hip", "fwd_d8.hip",
-           "bwd.hip", "bwd_dkdv.hip", "bwd_dq.hip", "bwd_short.hip", "fwd_short.hip", "merge.hip"]
+SOURCES = ["api.hip", "fwd.hip", "fwd_d64.hip", "fwd_d32.hip", "fwd_d16.hip", "fwd_d8.hip", "fwd_f32.hip",
+           "bwd.hip", "bwd_dkdv.hip", "bwd_dq.hip", "bwd_short.hip", "bwd_f32.hip", "fwd_short.hip", "merge.hip"]
 ARCH = os.environ.get("GT_OFFLOAD_ARCH", "gfx950")
 
 

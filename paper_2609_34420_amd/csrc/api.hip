@@ -26,8 +26,8 @@ inline bool dtype_ok(gt_dtype_t t) { return t == GT_F32 || t == GT_BF16; }
 
 inline bool scale_ok(float s) { return std::isfinite(s) && s > 0.0f; }
 
-// Whether every 16-key group of every spd row starts on a multiple of n bytes
-// (n = 16, 4).
+// Whether every spd row (from its first key on) starts on a multiple of n
+// bytes (n = 16, 4).
 inline int spd_aligned(const uint8_t* spd, int64_t ld, int64_t row_off, int64_t col_off, int64_t bstride,
                        unsigned n) {
   const uintptr_t base = reinterpret_cast<uintptr_t>(spd) + (uintptr_t)(row_off * ld + col_off);
@@ -76,7 +76,6 @@ static gt_status_t ring_impl(const void* q_shard, int64_t Sq, const void* k_shar
   a.table = table; a.n_buckets = n_buckets;
   a.o = o_part; a.lse = lse_part;
   a.H = H; a.Sq = Sq; a.Sk = Sk; a.scale = scale;
-  a.spd_vec = Sk > 0 ? spd_aligned(spd, ld_spd, row_off, col_off, 0, 16) : 0;
   a.spd_dw = Sk > 0 ? spd_aligned(spd, ld_spd, row_off, col_off, 0, 4) : 1;
   a.accumulate = accumulate;
   a.hpb = H; a.spd_bstride = 0;
@@ -125,7 +124,6 @@ static gt_status_t fwd_impl(const void* q, const void* k, const void* v, const u
   a.o = o; a.lse = lse;
   a.H = (int32_t)HT; a.Sq = N; a.Sk = N; a.scale = scale;
   a.hpb = H; a.spd_bstride = spd_bstride;
-  a.spd_vec = spd_aligned(spd, N, 0, 0, spd_bstride, 16);
   a.spd_dw = spd_aligned(spd, N, 0, 0, spd_bstride, 4);
   return launched(gt::launch_fwd(a, d, dtype == GT_BF16, dtype == GT_F32, static_cast<hipStream_t>(stream)));
 }
@@ -190,7 +188,6 @@ static gt_status_t bwd_impl(int32_t phase, const void* q, const void* k, const v
   a.H = H; a.Sq = N; a.Sk = N; a.scale = scale;
   a.row_off = 0; a.col_off = 0; a.accumulate = 0;
   a.hpb = Hh; a.spd_bstride = spd_bstride;
-  a.spd_vec = spd_aligned(spd, N, 0, 0, spd_bstride, 16);
   a.spd_dw = spd_aligned(spd, N, 0, 0, spd_bstride, 4);
   // The transpose is used only where its rows can be read 16 bytes at a time
   // and one key block's rows (256 of them) stay within 32-bit offsets.
@@ -328,7 +325,6 @@ gt_status_t gt_attn_bwd_ring_step(const void* q_shard, const void* o_shard, cons
   a.hpb = H; a.spd_bstride = 0;
   a.H = H; a.Sq = Sq; a.Sk = Sk; a.scale = scale;
   a.accumulate = 1;
-  a.spd_vec = spd_aligned(spd, ld_spd, row_off, col_off, 0, 16);
   a.spd_dw = spd_aligned(spd, ld_spd, row_off, col_off, 0, 4);
   return launched(gt::launch_bwd(a, d, dtype == GT_BF16, -1, static_cast<hipStream_t>(stream)));
 }

@@ -178,129 +178,4 @@ __device__ __forceinline__ void align_spd5(uint32_t (&w)[5], uint32_t sh) {
   for (int i = 0; i < 4; ++i) w[i] = __builtin_amdgcn_alignbyte(w[i + 1], w[i], sh);
 }
 
-// 16 spd bytes row[j .. j+15] as four dwords, byte by byte, bytes at or past
-// `limit` read as 0. Used for unaligned slices and the last partial group;
-// kept rolled so it costs few registers.
-__device__ __forceinline__ void load_spd16_bytes(const uint8_t* row, int64_t j, int64_t limit,
-                                                 uint32_t* w) {
-  uint64_t lo = 0, hi = 0;
-  const int64_t n = limit - j < 16 ? limit - j : 16;
-#pragma unroll 1
-  for (int t = 0; t < (int)n; ++t) {
-    const uint64_t b = row[j + t];
-    if (t < 8)
-      lo |= b << (8 * t);
-    else
-      hi |= b << (8 * (t - 8));
-  }
-  w[0] = (uint32_t)lo; w[1] = (uint32_t)(lo >> 32);
-  w[2] = (uint32_t)hi; w[3] = (uint32_t)(hi >> 32);
-}
-
-
-// spd bytes j .. j + KB - 1 (KB = 16 or 8) of a row into w (bytes past
-// `limit` as 0, words past the block 0): one aligned load of KB bytes when
-// `vec` (the whole block in range and the row 16-byte aligned), else bytes.
-template <int KB>
-__device__ __forceinline__ void load_spd_block(const uint8_t* row, int64_t j, int64_t limit, bool vec,
-                                               uint32_t w[4]) {
-  static_assert(KB == 16 || KB == 8, "spd block of 8 or 16 bytes");
-  if (vec) {
-    if constexpr (KB == 16) {
-      const uint4 v4 = *reinterpret_cast<const uint4*>(row + j);
-      w[0] = v4.x; w[1] = v4.y; w[2] = v4.z; w[3] = v4.w;
-    } else {
-      const uint2 v2 = *reinterpret_cast<const uint2*>(row + j);
-      w[0] = v2.x; w[1] = v2.y; w[2] = 0; w[3] = 0;
-    }
-  } else {
-    load_spd16_bytes(row, j, limit - j < KB ? limit : j + KB, w);
-  }
-}
-
-// LDS tiles of the fp32 vector-ALU kernels. Each of the 16 threads of a row
-// reads its own block of GB consecutive tile rows, so at any one read the
-// threads are GB rows apart. Tile row r is kept at LDS row r + r / GB with a
-// row stride of D + 4 floats: thread s then reads LDS row s (GB + 1) + k,
-// and for D = 8, 16, 32, 64 the 16 threads' 16-byte reads fall in distinct
-// bank groups. Without the padding and the gap they would all hit the same
-// banks.
-template <int D>
-constexpr int valu_row_stride() { return D + 4; }
-template <int R, int GB>
-constexpr int valu_tile_rows() { return R + R / GB; }
-template <int GB>
-__device__ __forceinline__ int valu_row(int r) { return r + r / GB; }
-
-// Rows r0 .. r0 + R - 1 of two row-major fp32 [nrows, D] tensors into LDS
-// tiles (the layout above) by NT threads, rows past nrows as zero, in
-// 16-byte loads and stores. x and y are 16-byte aligned: the entry points
-// reject unaligned tensors, and a head's rows start at a multiple of 16
-// bytes since D is a multiple of 4.
-template <int R, int D, int GB, int NT>
-__device__ __forceinline__ void stage_rows_f32(const float* x, const float* y, int64_t r0, int64_t nrows,
-                                               float (*sx)[valu_row_stride<D>()],
-                                               float (*sy)[valu_row_stride<D>()]) {
-  static_assert(D % 4 == 0, "rows of whole 16-byte chunks");
-  for (int t = (int)threadIdx.x; t < R * D / 4; t += NT) {
-    const int r = t / (D / 4), c = (t % (D / 4)) * 4;
-    float4 u = make_float4(0.0f, 0.0f, 0.0f, 0.0f), v = u;
-    if (r0 + r < nrows) {
-      u = *reinterpret_cast<const float4*>(x + (r0 + r) * D + c);
-      v = *reinterpret_cast<const float4*>(y + (r0 + r) * D + c);
-    }
-    *reinterpret_cast<float4*>(&sx[valu_row<GB>(r)][c]) = u;
-    *reinterpret_cast<float4*>(&sy[valu_row<GB>(r)][c]) = v;
-  }
-}
-
-// The same tiles through registers: load() issues the 16-byte loads of a
-// tile, store() writes them to LDS, so the loads of the next tile are in
-// flight while the current one is computed (2 R D / NT floats per thread).
-template <int R, int D, int GB, int NT>
-struct RowPrefetchF32 {
-  static_assert(D % 4 == 0 && (R * D / 4) % NT == 0, "whole 16-byte chunks, evenly over the threads");
-  static constexpr int N = R * D / 4 / NT;
-  float4 u[N], v[N];
-  __device__ __forceinline__ void load(const float* x, const float* y, int64_t r0, int64_t nrows) {
-#pragma unroll
-    for (int s = 0; s < N; ++s) {
-      const int t = (int)threadIdx.x + s * NT;
-      const int r = t / (D / 4), c = (t % (D / 4)) * 4;
-      u[s] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-      v[s] = u[s];
-      if (r0 + r < nrows) {
-        u[s] = *reinterpret_cast<const float4*>(x + (r0 + r) * D + c);
-        v[s] = *reinterpret_cast<const float4*>(y + (r0 + r) * D + c);
-      }
-    }
-  }
-  __device__ __forceinline__ void store(float (*sx)[valu_row_stride<D>()], float (*sy)[valu_row_stride<D>()]) const {
-#pragma unroll
-    for (int s = 0; s < N; ++s) {
-      const int t = (int)threadIdx.x + s * NT;
-      const int r = t / (D / 4), c = (t % (D / 4)) * 4;
-      *reinterpret_cast<float4*>(&sx[valu_row<GB>(r)][c]) = u[s];
-      *reinterpret_cast<float4*>(&sy[valu_row<GB>(r)][c]) = v[s];
-    }
-  }
-};
-
-// Row `row` of a row-major fp32 [*, D] tensor (16-byte aligned rows) times
-// `mul` into registers, or zeros when !ok. The row is read unconditionally
-// (callers pass a valid row, clamped when !ok) in 16-byte loads that are
-// all in flight together, rather than one guarded load and wait per element.
-template <int D>
-__device__ __forceinline__ void load_row_f32(const float* base, int64_t row, bool ok, float mul, float (&out)[D]) {
-  const float4* p = reinterpret_cast<const float4*>(base + row * D);
-  const float f = ok ? mul : 0.0f;
-#pragma unroll
-  for (int c = 0; c < D / 4; ++c) {
-    const float4 x = p[c];
-    out[4 * c] = x.x * f;
-    out[4 * c + 1] = x.y * f;
-    out[4 * c + 2] = x.z * f;
-    out[4 * c + 3] = x.w * f;
-  }
-}
 }  // namespace gt

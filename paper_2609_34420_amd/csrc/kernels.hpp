@@ -24,8 +24,7 @@ struct FwdArgs {
   int64_t Sq;
   int64_t Sk;
   float scale;            // multiplies Q K^T
-  int32_t spd_vec;        // every 16-byte spd group is 16-byte aligned
-  int32_t spd_dw;         // ... starts on a dword boundary
+  int32_t spd_dw;         // every row of spd starts on a dword boundary
   int32_t accumulate;     // 1 (fp32 outputs only): o, lse hold a running merged state and
                           // this block is merged into it in place
   int32_t hpb;            // heads per sequence: "head" h of H is head h % hpb of sequence h / hpb
@@ -62,8 +61,7 @@ struct BwdArgs {
   int64_t Sq;
   int64_t Sk;
   float scale;
-  int32_t spd_vec;        // every 16-byte spd group of the block is 16-byte aligned
-  int32_t spd_dw;         // ... starts on a dword boundary
+  int32_t spd_dw;         // every row of spd starts on a dword boundary
   int32_t accumulate;     // 1: dq, dk, dv are fp32 and receive +=; dtable is not cleared
   int32_t hpb;            // heads per sequence: "head" h of H is head h % hpb of sequence h / hpb
                           // (table and dtable rows are per head, shared by the sequences)
@@ -109,6 +107,12 @@ bool fwd_short_applies(const FwdArgs& a, int d);
 hipError_t launch_fwd_short_bf16(const FwdArgs& a, int d, hipStream_t s);
 // phase: -1 = all stages in order, 0 = prepare, 1 = dK/dV/dtable, 2 = dQ.
 hipError_t launch_bwd(const BwdArgs& a, int d, bool bf16, int phase, hipStream_t s);
+// fp32 inputs: the forward, dK/dV, and dQ with the table gradient, on the fp32
+// matrix cores; and the number of groups their workgroups' waves form.
+hipError_t launch_fwd_f32(const FwdArgs& a, int d, hipStream_t s);
+hipError_t launch_dkdv_f32(const BwdArgs& a, int d, hipStream_t s);
+hipError_t launch_dq_f32(const BwdArgs& a, int d, hipStream_t s);
+int pick_split_f32(int64_t rows, int64_t cols, int64_t heads, int D);
 hipError_t launch_dkdv_bf16(const BwdArgs& a, int d, hipStream_t s);
 hipError_t launch_dq_bf16(const BwdArgs& a, int d, hipStream_t s);
 // Sequences of at most 256 rows (bf16, d <= 32, not a ring step): the whole

@@ -94,3 +94,63 @@ def run_case(dt, H, Sq, Sk, d, first, pad, nb):
 @pytest.mark.parametrize("H,Sq,Sk,d,first,pad,nb", CASES)
 def test_any_size_bf16(H, Sq, Sk, d, first, pad, nb):
     run_case("bf16", H, Sq, Sk, d, first, pad, nb)
+
+
+@pytest.mark.parametrize("H,Sq,Sk,d,first,pad,nb", CASES)
+def test_any_size_f32(H, Sq, Sk, d, first, pad, nb):
+    run_case("f32", H, Sq, Sk, d, first, pad, nb)
+
+
+def test_f32_nonfinite_gradients():
+    """fp32: a NaN dO row reaches every bucket its row holds, and no other; a
+    row whose every score is -inf contributes nothing, whatever its dO."""
+    H, N, d, nb = 2, 200, 32, 12
+    g = np.random.default_rng(3)
+    spd = g.integers(1, 8, size=(N, N)).astype(np.uint8)
+    spd[5] = g.integers(8, 11, size=N)           # buckets 8..10: row 5 only
+    spd[9] = 0                                   # bucket 0 is -inf: row 9 has no score
+    table = (g.standard_normal((H, nb)) * 0.5).astype(np.float32)
+    table[:, 0] = -np.inf
+    q, k, v, do = (to_dev(g.standard_normal((H, N, d)).astype(np.float32)) for _ in range(4))
+    S, T = to_dev(spd, torch.uint8), to_dev(table)
+    o, l = gt.gt_attn_fwd(q, k, v, S, T)
+    ref = gt.gt_attn_bwd(q, k, v, S, T, o, l, do)
+    do[:, 9] = float("nan")
+    got = gt.gt_attn_bwd(q, k, v, S, T, o, l, do)
+    for a, b in zip(ref[:3], got[:3]):
+        assert torch.equal(a, b)
+    assert torch.allclose(ref[3], got[3], rtol=1e-5, atol=1e-5) and bool(torch.isfinite(got[3]).all())
+    do[:, 5] = float("nan")
+    dtab = gt.gt_attn_bwd(q, k, v, S, T, o, l, do)[3]
+    assert bool(torch.isnan(dtab[:, 8:11]).all())
+    assert torch.allclose(dtab[:, 11], torch.zeros_like(dtab[:, 11]))
+
+
+@pytest.mark.parametrize("B,H,N,d", [
+    (65, 32, 32, 8), (70, 32, 31, 32), (37, 64, 33, 16), (33, 64, 64, 64), (40, 32, 65, 64), (35, 32, 128, 8),
+    (259, 8, 17, 64),
+])
+def test_f32_packed_batch(B, H, N, d):
+    """fp32 batches of sequences of at most 128, 64 and 32 rows, of which a
+    workgroup takes 2, 4 or 8, the last one a partly filled group."""
+    g = np.random.default_rng(B + N)
+    nb = 12
+    spd = g.integers(0, nb + 2, size=(B, N, N)).astype(np.uint8)
+    q, k, v, do = (g.standard_normal((B, H, N, d)).astype(np.float32) for _ in range(4))
+    table = (g.standard_normal((H, nb)) * 0.5).astype(np.float32)
+    scale = 1.0 / np.sqrt(d)
+    say(f"packed f32 B={B} H={H} N={N} d={d}")
+    Q, K, V, dO, S, T = to_dev(q), to_dev(k), to_dev(v), to_dev(do), to_dev(spd, torch.uint8), to_dev(table)
+    o, l = gt.gt_attn_fwd_batch(Q, K, V, S, T)
+    got = gt.gt_attn_bwd_batch(Q, K, V, S, T, o, l, dO)
+    torch.cuda.synchronize()
+    dtab = np.zeros((H, nb))
+    for b in list(range(0, B, 7)) + [B - 1]:
+        o_ref, l_ref = oracle.forward(q[b], k[b], v[b], spd[b], table, scale)
+        check_fwd(f"graph {b}", to_np(o[b]), to_np(l[b]), o_ref, l_ref, "f32")
+        ref = oracle.backward(q[b], k[b], v[b], spd[b], table, scale, do[b])
+        check_grads(f"graph {b}", dict(dq=to_np(got[0][b]), dk=to_np(got[1][b]), dv=to_np(got[2][b])),
+                    dict(dq=ref[0], dk=ref[1], dv=ref[2]), "f32")
+    for b in range(B):
+        dtab += oracle.backward(q[b], k[b], v[b], spd[b], table, scale, do[b])[3]
+    check_grads("dtable", dict(dtable=to_np(got[3])), dict(dtable=dtab), "f32")
