@@ -119,16 +119,16 @@ struct ShortOffsets {
 
 // Block (query block qb, this wave's keys): S and dP, P and dS, the bias
 // reads and gradient adds, dV and dK, and dS (bf16) into slot xs.
-// b: the lane's 16 bucket indices (4 words of spd_t, or 16 gathered bytes).
+// b: the lane's 16 bucket indices.
 // SPROD: the statistics come with the products (features DS..DS+2 of the Q
 // and dO rows hold -LSE / scale and -Dlt, and the lane's K and V operands
 // ones and 2^F there; NKS then counts the chunk that holds them), so S and dP
 // start from zero.
 // rb: first LDS row of the wave's sequence (its slice when several
 // sequences share the workgroup).
-template <int NKS, int NB, bool SPROD, typename BT>
+template <int NKS, int NB, bool SPROD>
 __device__ __forceinline__ void block_dkdv(ShortSmem<NB>& sm, const ShortOffsets& off,
-                                           const bf16x8* kf, const bf16x8* vf, const BT* b,
+                                           const bf16x8* kf, const bf16x8* vf, const uint32_t* b,
                                            const float* is_lane, float sl2, int rb, int qb, uint16_t* xs,
                                            f32x16& dk, f32x16& dv) {
   const int lane = threadIdx.x & 63;
@@ -160,27 +160,10 @@ __device__ __forceinline__ void block_dkdv(ShortSmem<NB>& sm, const ShortOffsets
   constexpr int CPY = copies<NB>();
   const uint32_t cpyb = (uint32_t)(lane & (CPY - 1)) * 8u | kTabBase;
   uint32_t w[4];
-  if constexpr (sizeof(BT) == 4) {
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      w[u] = b[u];
-      opaque(w[u]);
-    }
-  } else {
-    // 16 gathered bytes (one per register, upper bits unknown to the
-    // compiler) packed into 4 words by byte permutes
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      uint32_t x[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        x[e] = b[4 * u + e];
-        opaque(x[e]);
-      }
-      const uint32_t lo = __builtin_amdgcn_perm(x[1], x[0], 0x0c0c0400u);
-      const uint32_t hi = __builtin_amdgcn_perm(x[3], x[2], 0x0c0c0400u);
-      w[u] = __builtin_amdgcn_perm(hi, lo, 0x05040100u);
-    }
+  for (int u = 0; u < 4; ++u) {
+    w[u] = b[u];
+    opaque(w[u]);
   }
   clamp_buckets<NB>(w);
 #pragma unroll
@@ -219,19 +202,23 @@ __device__ __forceinline__ void block_dkdv(ShortSmem<NB>& sm, const ShortOffsets
   }
 }
 
-// STAGE (no transpose given, spd rows 4-byte aligned): the spd block of a
-// step is loaded row-wise, 16 bytes per lane (lane l: row l / 2, bytes
-// 16 (l % 2) .. + 15 of the block's 32 x 32), written to the first KiB of
-// the wave's dS slot of that step (free until the block's dS is stored
+// READ: kTrans takes a key's 16 query bytes from a row of spd_t. Otherwise
+// the spd block of a step is loaded row-wise, 16 bytes per lane (lane l: row
+// l / 2, bytes 16 (l % 2) .. + 15 of the block's 32 x 32), written to the first
+// KiB of the wave's dS slot of that step (free until the block's dS is stored
 // there), and each lane reads its key's 16 query bytes back with two 8-bit
-// transposing LDS reads, instead of 16 byte gathers from global memory.
+// transposing LDS reads. kRowsDw: spd rows on dword boundaries; kRowsAny: at
+// any address, loaded as the 5 dwords that hold the 16 bytes and aligned in
+// registers (512 x 203 nodes, H = 8, d = 32: 271 us, 316 with a gather of 16
+// bytes per key).
 // SPROD (head dims 8 and 16, N a multiple of 32): the S and dP accumulators
 // start at zero, and -LSE / scale, -Dlt enter the products through the
 // zero-padded features DS..DS+2 (three bf16 terms each, exact to about 2^-24)
 // of the staged Q and dO rows against ones and 2^F in the lane's K and V
 // operands, instead of eight LDS reads of statistics per block (at DS = 16
 // one more 16-feature chunk of S and dP).
-template <int DS, int NB, bool TR, bool STAGE, bool SPROD = false>
+enum SpdRead { kTrans = 0, kRowsDw = 1, kRowsAny = 2 };
+template <int DS, int NB, SpdRead READ, bool SPROD = false>
 __global__ __launch_bounds__(kThreads, 1) void bwd_short_bf16_kernel(BwdArgs a) {
   constexpr int NKS = (DS + 15) / 16;   // 16-feature chunks of S and dP that hold data
   constexpr int CPS = DS / 8;           // 16-byte chunks per source row
@@ -285,9 +272,7 @@ __global__ __launch_bounds__(kThreads, 1) void bwd_short_bf16_kernel(BwdArgs a) 
   const float* is_lane = (jok ? sm.init_s : sm.ninf) + 16 * g;
   const ShortOffsets off;
   const int ld = (int)a.ld_spd;
-  using BT = std::conditional_t<TR || STAGE, uint32_t, uint8_t>;
-  constexpr int NBT = TR || STAGE ? 4 : 16;
-  static_assert(!(TR && STAGE), "one way of reading spd");
+  constexpr int NBT = READ == kRowsAny ? 6 : 4;   // kRowsAny: 5 dwords and their address mod 4
   static_assert(!SPROD || DS <= 16, "statistics through the padded features need DS <= 16");
   constexpr int NKSP = SPROD ? (DS + 3 + 15) / 16 : NKS;   // chunks of S and dP with the statistics
 
@@ -419,18 +404,24 @@ __global__ __launch_bounds__(kThreads, 1) void bwd_short_bf16_kernel(BwdArgs a) 
 #pragma unroll
   for (int hh = 0; hh < 2; ++hh)
     off_tr8[hh] = (16 * g + 8 * hh + ((lane & 15) >> 1)) * 32 + 16 * ((lane >> 4) & 1) + 8 * (lane & 1);
-  auto fetch = [&](int s, int qb, BT* dst) {
+  auto fetch = [&](int s, int qb, uint32_t (&dst)[NBT]) {
     const int h = s * a.hpb + head;
-    const __amdgpu_buffer_rsrc_t rs =
-        make_rsrc_n(TR ? seq_spd_t(a, h) : seq_spd(a, h), (int64_t)N * ld);
-    if constexpr (STAGE) {
-      buf_u128(rs, voff_st, (uint32_t)(qb * 32 * ld), reinterpret_cast<uint32_t*>(dst));
-    } else if constexpr (TR) {
-      buf_u128(rs, (uint32_t)(jc * ld + 16 * g), (uint32_t)(qb * 32), reinterpret_cast<uint32_t*>(dst));
+    if constexpr (READ == kTrans) {
+      const __amdgpu_buffer_rsrc_t rs = make_rsrc_n(seq_spd_t(a, h), (int64_t)N * ld);
+      buf_u128(rs, (uint32_t)(jc * ld + 16 * g), (uint32_t)(qb * 32), dst);
     } else {
-      const uint32_t voff = (uint32_t)((qb * 32 + 16 * g) * ld + jc);
+      uint32_t rem;
+      const __amdgpu_buffer_rsrc_t rs = spd_rsrc<READ == kRowsAny>(seq_spd(a, h), (int64_t)(N - 1) * ld + N, rem);
+      if constexpr (READ == kRowsAny) {
+        const uint32_t v = voff_st + rem;
+        uint32_t w5[5];
+        load_spd5(rs, v & ~3u, (uint32_t)(qb * 32 * ld), w5);
 #pragma unroll
-      for (int r = 0; r < 16; ++r) dst[r] = (uint8_t)buf_u8(rs, voff, (uint32_t)(r * ld));
+        for (int u = 0; u < 5; ++u) dst[u] = w5[u];
+        dst[5] = v & 3u;
+      } else {
+        buf_u128(rs, voff_st, (uint32_t)(qb * 32 * ld), dst);
+      }
     }
   };
 
@@ -441,7 +432,7 @@ __global__ __launch_bounds__(kThreads, 1) void bwd_short_bf16_kernel(BwdArgs a) 
   int fexp = 40;
   bool used = false;
 
-  BT bA[NBT], bB[NBT];
+  uint32_t bA[NBT], bB[NBT];
   issue(slot);
   fetch(clamp_seq(seq_of(slot)), wl, bA);
   stats();
@@ -540,14 +531,21 @@ __global__ __launch_bounds__(kThreads, 1) void bwd_short_bf16_kernel(BwdArgs a) 
 
     f32x16 dk = zero_f32x16(), dv = zero_f32x16(), dq = zero_f32x16();
     const bool wact = wl < nb && seq < nseq;
-    auto step_a = [&](int t, uint16_t* xs, const BT* b) {
+    auto step_a = [&](int t, uint16_t* xs, const uint32_t (&b)[NBT]) {
       const int qb = (wl + t) & (GW - 1);
       if (wact && qb < nb) {
-        if constexpr (STAGE) {
+        if constexpr (READ != kTrans) {
           typedef int i32x2 __attribute__((ext_vector_type(2)));
           typedef __attribute__((address_space(3))) i32x2* lds_i32x2;
           uint8_t* st8 = reinterpret_cast<uint8_t*>(xs);
-          uint4 v4 = make_uint4(b[0], b[1], b[2], b[3]);
+          uint4 v4;
+          if constexpr (READ == kRowsAny) {
+            uint32_t w5[5] = {b[0], b[1], b[2], b[3], b[4]};
+            align_spd5(w5, b[5]);
+            v4 = make_uint4(w5[0], w5[1], w5[2], w5[3]);
+          } else {
+            v4 = make_uint4(b[0], b[1], b[2], b[3]);
+          }
           opaque(v4);
           *reinterpret_cast<uint4*>(st8 + 16 * lane) = v4;
           uint32_t wv[4];
@@ -657,26 +655,23 @@ void launch_short_t(const BwdArgs& a, hipStream_t s) {
   if (slots < 1) slots = 1;
   if (slots > ngroups) slots = ngroups;
   const dim3 grid((unsigned)(slots * a.hpb));
-  // row-wise staging reads 16 bytes from 4-byte aligned offsets
-  const bool rows4 = reinterpret_cast<uintptr_t>(a.spd) % 4 == 0 && a.ld_spd % 4 == 0 &&
-                     a.spd_bstride % 4 == 0;
   if constexpr (DS <= 16) {
     if (a.Sq % 32 == 0) {     // no keys past N in any block
       if (a.spd_t)
-        hipLaunchKernelGGL((bwd_short_bf16_kernel<DS, NB, true, false, true>), grid, dim3(kThreads), 0, s, a);
-      else if (rows4)
-        hipLaunchKernelGGL((bwd_short_bf16_kernel<DS, NB, false, true, true>), grid, dim3(kThreads), 0, s, a);
+        hipLaunchKernelGGL((bwd_short_bf16_kernel<DS, NB, kTrans, true>), grid, dim3(kThreads), 0, s, a);
+      else if (a.spd_dw)
+        hipLaunchKernelGGL((bwd_short_bf16_kernel<DS, NB, kRowsDw, true>), grid, dim3(kThreads), 0, s, a);
       else
-        hipLaunchKernelGGL((bwd_short_bf16_kernel<DS, NB, false, false, true>), grid, dim3(kThreads), 0, s, a);
+        hipLaunchKernelGGL((bwd_short_bf16_kernel<DS, NB, kRowsAny, true>), grid, dim3(kThreads), 0, s, a);
       return;
     }
   }
   if (a.spd_t)
-    hipLaunchKernelGGL((bwd_short_bf16_kernel<DS, NB, true, false>), grid, dim3(kThreads), 0, s, a);
-  else if (rows4)
-    hipLaunchKernelGGL((bwd_short_bf16_kernel<DS, NB, false, true>), grid, dim3(kThreads), 0, s, a);
+    hipLaunchKernelGGL((bwd_short_bf16_kernel<DS, NB, kTrans>), grid, dim3(kThreads), 0, s, a);
+  else if (a.spd_dw)
+    hipLaunchKernelGGL((bwd_short_bf16_kernel<DS, NB, kRowsDw>), grid, dim3(kThreads), 0, s, a);
   else
-    hipLaunchKernelGGL((bwd_short_bf16_kernel<DS, NB, false, false>), grid, dim3(kThreads), 0, s, a);
+    hipLaunchKernelGGL((bwd_short_bf16_kernel<DS, NB, kRowsAny>), grid, dim3(kThreads), 0, s, a);
 }
 
 template <int NB>

@@ -191,9 +191,8 @@ __device__ __forceinline__ void softmax_first(const f32x16& s, const bf16x8 (&vo
   }
 }
 
-// Persistent forward for sequences of at most 256 rows, N a multiple of 4,
-// with at most 127 buckets (bf16 in and out, head dims 8, 16, 32 on 32-wide
-// tiles; spd rows 4-byte aligned). Each wave owns 32 queries, and the
+// Persistent forward for sequences of at most 256 rows with at most 127
+// buckets (bf16 in and out, head dims 8, 16, 32 on 32-wide tiles). Each wave owns 32 queries, and the
 // sequence's K and V (all rows) sit in LDS: one pair of barriers per
 // sequence instead of one barrier per key tile. At N > 128 a workgroup
 // covers one sequence; shorter ones are packed, 2, 4 or 8 sequences of the
@@ -209,11 +208,18 @@ __device__ __forceinline__ void softmax_first(const f32x16& s, const bf16x8 (&vo
 // groups (read 16 bytes at a time from 4-byte aligned offsets, through a
 // resource that ends with the sequence's matrix); the score product of key
 // block kb + 1 is issued before the softmax of block kb. TAIL: keys past N
-// in the last block (N not a multiple of 32, or N <= 32).
+// in the last block (N not a multiple of 32, or N <= 32). ANY: spd rows at any
+// address, loaded as the 5 dwords that hold each group and aligned in registers
+// (N not a multiple of 4; TAIL goes with it). H = 8, against the full-width
+// forward that took these before (its 64 KB table filled per workgroup and one
+// workgroup per compute unit): 512 x 203 nodes, d = 32 206 -> 106 us, 8192 x 30, d = 8
+// 3790 -> 88; d = 64: 512 x 256 247 -> 177, 4000 x 33 2242 -> 148.
 constexpr int kShortTabEntries = 129;
-template <int DS, bool TAIL>
+template <int DS, bool TAIL, bool ANY>
 __global__ __launch_bounds__(kThreads, DS <= 16 ? 4 : 2) void fwd_short_bf16_kernel(FwdArgs a) {
-  constexpr int D = 32;
+  constexpr int D = DS == 64 ? 64 : 32;
+  constexpr int CPR = D / 8;                    // 16-byte chunks per LDS row
+  constexpr int NWD = ANY ? 5 : 4;              // dwords of a spd group in flight
   constexpr int NKC = D / 16;
   constexpr int NKS = (DS + 15) / 16;
   constexpr int NCB = D / 32;
@@ -223,10 +229,10 @@ __global__ __launch_bounds__(kThreads, DS <= 16 ? 4 : 2) void fwd_short_bf16_ker
   constexpr int IPT = (PER + kThreads - 1) / kThreads;
   constexpr bool XP = DS == 8 && !TAIL;         // exponents from the score product
   constexpr int NKP = XP ? 2 : NKS;             // 16-feature chunks of the score product
-  // alternating score sets where registers allow: at d = 32 (one workgroup
+  // alternating score sets where registers allow: at d >= 32 (one workgroup
   // per compute unit) and at d = 8 without a partial key block; elsewhere
   // the copy keeps four waves per SIMD without spilling
-  constexpr bool ALT = DS == 32 || XP;
+  constexpr bool ALT = DS >= 32 || XP;
   // Padding rows (zero): the K rows of block nkb mod 8, read past the last
   // block of a sequence (the product is never used), and at N <= 32 the K
   // and V rows of the masked second block of the last slice stay in the
@@ -279,7 +285,7 @@ __global__ __launch_bounds__(kThreads, DS <= 16 ? 4 : 2) void fwd_short_bf16_ker
     }
     constexpr uint32_t kOne = 0x3f80u;           // bf16 1.0
     for (int t = tid; t < KROWS * D / 8; t += kThreads) {
-      const int row = t >> 2, ch = t & 3;
+      const int row = t / CPR, ch = t % CPR;
       const int lo = row * D + swz_tile<D>(row, ch) * 8;
       const bool k1 = XP && ch == 3, v1 = XP && ch == 1;
       *reinterpret_cast<uint4*>(sK + lo) = make_uint4(k1 ? kOne | (kOne << 16) : 0u, k1 ? kOne : 0u, 0u, 0u);
@@ -327,19 +333,32 @@ __global__ __launch_bounds__(kThreads, DS <= 16 ? 4 : 2) void fwd_short_bf16_ker
                                         : zero_bf16x8();
     }
   };
-  auto spd_rs = [&](int s) {
+  auto spd_rs = [&](int s, uint32_t& rem) {
     const int h = s * a.hpb + head;
-    return make_rsrc_n(seq_spd(a, h), (int64_t)N * ld);
+    return spd_rsrc<ANY>(seq_spd(a, h), (int64_t)(N - 1) * ld + N, rem);
   };
   const uint32_t voff = (uint32_t)(qc * ld + 16 * g);
+  // Words of the key block at byte j of the lane's row (ANY: at any address,
+  // as the 5 dwords that hold them).
+  auto spd_load = [&](const __amdgpu_buffer_rsrc_t& r, uint32_t rem, uint32_t j, uint32_t (&w)[NWD]) {
+    if constexpr (ANY)
+      load_spd5(r, (voff + rem) & ~3u, j, w);
+    else
+      buf_u128(r, voff, j, w);
+  };
   // Bucket words of key block kb as table entries: bytes of 128 or more to
   // the padding entry 127; with TAIL, keys past N to the -inf entry.
-  auto entries = [&](const uint32_t (&wsrc)[4], int kb, uint32_t (&e)[4]) {
+  uint32_t sh = 0;                              // ANY: this sequence's row address mod 4
+  auto entries = [&](const uint32_t (&wsrc)[NWD], int kb, uint32_t (&e)[4]) {
+    uint32_t x[NWD];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      e[u] = wsrc[u];
-      opaque(e[u]);
+    for (int u = 0; u < NWD; ++u) {
+      x[u] = wsrc[u];
+      opaque(x[u]);
     }
+    if constexpr (ANY) align_spd5(x, sh);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) e[u] = x[u];
     if (__any(((e[0] | e[1] | e[2] | e[3]) & 0x80808080u) != 0)) {
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
@@ -351,15 +370,24 @@ __global__ __launch_bounds__(kThreads, DS <= 16 ? 4 : 2) void fwd_short_bf16_ker
       }
     }
     if constexpr (TAIL) {
+      if constexpr (!ANY) {      // rows on dword boundaries: N is a multiple of 4
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (kb * 32 + 16 * g + 4 * u >= N) e[u] = 0x80808080u;   // N is a multiple of 4
+        for (int u = 0; u < 4; ++u)
+          if (kb * 32 + 16 * g + 4 * u >= N) e[u] = 0x80808080u;
+      } else if (kb * 32 + 32 > N) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int n = N - (kb * 32 + 16 * g + 4 * u);         // valid keys of the word
+          const uint32_t keep = n >= 4 ? 0xffffffffu : (n <= 0 ? 0u : (1u << (8 * n)) - 1u);
+          e[u] = (e[u] & keep) | (0x80808080u & ~keep);
+        }
+      }
     }
   };
 
   SoftmaxState st;
   f32x16 acc[NCB];
-  uint32_t wd[3][4];                              // spd words of key blocks kb, kb + 1, kb + 2
+  uint32_t wd[3][NWD];                            // spd words of key blocks kb, kb + 1, kb + 2
 
   // One group: its K, V, Q are in registers on entry (loaded during the
   // previous one), and wd[0], wd[1] hold the first spd words of the wave's
@@ -370,8 +398,10 @@ __global__ __launch_bounds__(kThreads, DS <= 16 ? 4 : 2) void fwd_short_bf16_ker
     const int s = seq_of(gi);
     const bool wact = wrows && s < nseq;
     const int gnx = gi + nslots < ngroups ? gi + nslots : gi;
-    const __amdgpu_buffer_rsrc_t rs = spd_rs(clamp_seq(s));
-    const __amdgpu_buffer_rsrc_t rn = spd_rs(clamp_seq(seq_of(gnx)));
+    uint32_t rem_s, rem_n;
+    const __amdgpu_buffer_rsrc_t rs = spd_rs(clamp_seq(s), rem_s);
+    const __amdgpu_buffer_rsrc_t rn = spd_rs(clamp_seq(seq_of(gnx)), rem_n);
+    if constexpr (ANY) sh = (voff + rem_s) & 3u;
     __syncthreads();            // the previous group's reads of K and V are done
 #pragma unroll
     for (int i = 0; i < IPT; ++i) {
@@ -418,7 +448,7 @@ __global__ __launch_bounds__(kThreads, DS <= 16 ? 4 : 2) void fwd_short_bf16_ker
         const int kf = kb + 2;
         const bool here = kf < nkb;
         const __amdgpu_buffer_rsrc_t src = here ? rs : rn;
-        buf_u128(src, voff, (uint32_t)((here ? kf : kf - nkb) * 32), wd[(kb + 2) % 3]);
+        spd_load(src, here ? rem_s : rem_n, (uint32_t)((here ? kf : kf - nkb) * 32), wd[(kb + 2) % 3]);
       }
       sched_fence();
       if (wact) {
@@ -478,10 +508,10 @@ __global__ __launch_bounds__(kThreads, DS <= 16 ? 4 : 2) void fwd_short_bf16_ker
     // the next sequence's first two word sets sit in wd[nkb % 3], wd[(nkb + 1) % 3]
     if (nkb % 3 == 1) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) { const uint32_t t0 = wd[0][e]; wd[0][e] = wd[1][e]; wd[1][e] = wd[2][e]; wd[2][e] = t0; }
+      for (int e = 0; e < NWD; ++e) { const uint32_t t0 = wd[0][e]; wd[0][e] = wd[1][e]; wd[1][e] = wd[2][e]; wd[2][e] = t0; }
     } else if (nkb % 3 == 2) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) { const uint32_t t2 = wd[2][e]; wd[2][e] = wd[1][e]; wd[1][e] = wd[0][e]; wd[0][e] = t2; }
+      for (int e = 0; e < NWD; ++e) { const uint32_t t2 = wd[2][e]; wd[2][e] = wd[1][e]; wd[1][e] = wd[0][e]; wd[0][e] = t2; }
     }
     // epilogue: O = O_acc / l, LSE = (m + log2 l) ln 2
     if (wact) {
@@ -496,13 +526,16 @@ __global__ __launch_bounds__(kThreads, DS <= 16 ? 4 : 2) void fwd_short_bf16_ker
         const __amdgpu_buffer_rsrc_t ro =
             make_rsrc_n(reinterpret_cast<uint16_t*>(a.o) + (int64_t)h * N * DS, (int64_t)N * DS * 2);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int c = 8 * u + 4 * g;
-          if (c >= DS) continue;
-          u32x2 pk;
-          pk[0] = (uint32_t)f2bf(acc[0][4 * u] * inv) | ((uint32_t)f2bf(acc[0][4 * u + 1] * inv) << 16);
-          pk[1] = (uint32_t)f2bf(acc[0][4 * u + 2] * inv) | ((uint32_t)f2bf(acc[0][4 * u + 3] * inv) << 16);
-          __builtin_amdgcn_raw_buffer_store_b64(pk, ro, (uint32_t)((qi * DS + c) * 2), 0, 0);
+        for (int cb = 0; cb < NCB; ++cb) {
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const int c = cb * 32 + 8 * u + 4 * g;
+            if (c >= DS) continue;
+            u32x2 pk;
+            pk[0] = (uint32_t)f2bf(acc[cb][4 * u] * inv) | ((uint32_t)f2bf(acc[cb][4 * u + 1] * inv) << 16);
+            pk[1] = (uint32_t)f2bf(acc[cb][4 * u + 2] * inv) | ((uint32_t)f2bf(acc[cb][4 * u + 3] * inv) << 16);
+            __builtin_amdgcn_raw_buffer_store_b64(pk, ro, (uint32_t)((qi * DS + c) * 2), 0, 0);
+          }
         }
         if (g == 0) {
           const __amdgpu_buffer_rsrc_t rl = make_rsrc_n(a.lse + (int64_t)h * N, (int64_t)N * 4);
@@ -514,9 +547,10 @@ __global__ __launch_bounds__(kThreads, DS <= 16 ? 4 : 2) void fwd_short_bf16_ker
 
   issue(slot);
   {
-    const __amdgpu_buffer_rsrc_t rs = spd_rs(clamp_seq(seq_of(slot)));
-    buf_u128(rs, voff, 0u, wd[0]);
-    buf_u128(rs, voff, 32u, wd[1]);
+    uint32_t rem;
+    const __amdgpu_buffer_rsrc_t rs = spd_rs(clamp_seq(seq_of(slot)), rem);
+    spd_load(rs, rem, 0u, wd[0]);
+    spd_load(rs, rem, 32u, wd[1]);
   }
   for (int gi = slot; gi < ngroups; gi += nslots) run(gi);
   wait_vmcnt<0>();     // drain the loads issued for the last (repeated) sequence
@@ -532,10 +566,12 @@ void launch_short_t(const FwdArgs& a, hipStream_t s) {
   if (slots < 1) slots = 1;
   if (slots > ngroups) slots = ngroups;
   const dim3 grid((unsigned)(slots * a.hpb));
-  if (a.Sq % 32 != 0 || a.Sq <= 32)   // keys past N masked (at N <= 32 the whole second block)
-    hipLaunchKernelGGL((fwd_short_bf16_kernel<DS, true>), grid, dim3(kThreads), 0, s, a);
+  if (!a.spd_dw)
+    hipLaunchKernelGGL((fwd_short_bf16_kernel<DS, true, true>), grid, dim3(kThreads), 0, s, a);
+  else if (a.Sq % 32 != 0 || a.Sq <= 32)   // keys past N masked (at N <= 32 the whole second block)
+    hipLaunchKernelGGL((fwd_short_bf16_kernel<DS, true, false>), grid, dim3(kThreads), 0, s, a);
   else
-    hipLaunchKernelGGL((fwd_short_bf16_kernel<DS, false>), grid, dim3(kThreads), 0, s, a);
+    hipLaunchKernelGGL((fwd_short_bf16_kernel<DS, false, false>), grid, dim3(kThreads), 0, s, a);
 }
 
 }  // namespace
@@ -543,18 +579,17 @@ void launch_short_t(const FwdArgs& a, hipStream_t s) {
 bool fwd_short_applies(const FwdArgs& a, int d) {
   // (a group of up to 8 sequences is read through one resource of at most
   // 2^30 bytes)
-  return d <= 32 && !a.accumulate && a.row_off == 0 && a.col_off == 0 && a.Sq == a.Sk &&
-         a.Sq >= 1 && a.Sq <= 256 && a.Sq % 4 == 0 &&   // (keys past N are masked by spd words)
+  return !a.accumulate && a.row_off == 0 && a.col_off == 0 && a.Sq == a.Sk && a.Sq >= 1 && a.Sq <= 256 &&
          a.n_buckets <= 127 && a.hpb >= 1 && a.H % a.hpb == 0 &&
-         (int64_t)8 * a.hpb * a.Sq * d * 2 < ((int64_t)1 << 30) &&
-         reinterpret_cast<uintptr_t>(a.spd) % 4 == 0 && a.ld_spd % 4 == 0 && a.spd_bstride % 4 == 0;
+         (int64_t)8 * a.hpb * a.Sq * d * 2 < ((int64_t)1 << 30);
 }
 
 hipError_t launch_fwd_short_bf16(const FwdArgs& a, int d, hipStream_t s) {
   switch (d) {
     case 8: launch_short_t<8>(a, s); break;
     case 16: launch_short_t<16>(a, s); break;
-    default: launch_short_t<32>(a, s); break;
+    case 32: launch_short_t<32>(a, s); break;
+    default: launch_short_t<64>(a, s); break;
   }
   return hipGetLastError();
 }

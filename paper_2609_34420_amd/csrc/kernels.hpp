@@ -100,9 +100,8 @@ int fwd_key_split(const FwdArgs& a, int D);
 // The split ks = 1, 2 or 4 that finishes first, for workgroups of rows1 / ks
 // rows over tiles of tile1, tile2, tile4 columns.
 int pick_split(int64_t rows, int64_t cols, int64_t heads, int rows1, int tile1, int tile2, int tile4);
-// Sequences of at most 256 rows, N a multiple of 4 (bf16 in and out,
-// d <= 32, at most 127 buckets, spd rows 4-byte aligned): the persistent
-// whole-sequence forward.
+// Sequences of at most 256 rows (bf16 in and out, at most 127 buckets): the
+// persistent whole-sequence forward.
 bool fwd_short_applies(const FwdArgs& a, int d);
 hipError_t launch_fwd_short_bf16(const FwdArgs& a, int d, hipStream_t s);
 // phase: -1 = all stages in order, 0 = prepare, 1 = dK/dV/dtable, 2 = dQ.

@@ -154,3 +154,43 @@ def test_f32_packed_batch(B, H, N, d):
     for b in range(B):
         dtab += oracle.backward(q[b], k[b], v[b], spd[b], table, scale, do[b])[3]
     check_grads("dtable", dict(dtable=to_np(got[3])), dict(dtable=dtab), "f32")
+
+
+@pytest.mark.parametrize("B,H,N,d,first", [
+    (3, 2, 1, 64, 0), (9, 2, 3, 8, 1), (17, 4, 30, 8, 0), (11, 4, 31, 64, 0), (9, 8, 33, 16, 3), (7, 4, 47, 64, 0),
+    (5, 8, 63, 32, 0), (5, 2, 65, 64, 2), (5, 2, 129, 16, 0), (3, 2, 203, 32, 0), (3, 2, 255, 64, 1),
+    (3, 2, 256, 64, 0), (3, 2, 256, 8, 1), (2, 2, 200, 64, 0), (70, 8, 50, 64, 1),
+])
+def test_short_batch_any_size(B, H, N, d, first):
+    """bf16 batches on the whole-sequence kernels: lengths either side of the
+    packing limits, of the 32-key block and of the dword, head dim 64, and spd
+    matrices that start at an odd byte; several groups per workgroup."""
+    g = np.random.default_rng(N * 10 + d)
+    nb = 12
+    spd = g.integers(0, nb + 2, size=(B, N, N)).astype(np.uint8)
+    q, k, v, do = (synth.round_bf16(g.standard_normal((B, H, N, d)).astype(np.float32)) for _ in range(4))
+    table = (g.standard_normal((H, nb)) * 0.5).astype(np.float32)
+    scale = 1.0 / np.sqrt(d)
+    say(f"short bf16 B={B} H={H} N={N} d={d} first={first}")
+    bf = torch.bfloat16
+    Q, K, V, dO, T = to_dev(q, bf), to_dev(k, bf), to_dev(v, bf), to_dev(do, bf), to_dev(table)
+    buf = to_dev(np.concatenate([np.zeros(first, np.uint8), spd.ravel()]), torch.uint8)
+    S = buf[first:].view(B, N, N)
+    o, l = gt.gt_attn_fwd_batch(Q, K, V, S, T)
+    torch.cuda.synchronize()
+    o_in = np.zeros((B, H, N, d), np.float32)
+    l_in = np.zeros((B, H, N), np.float32)
+    refs = []
+    for b in range(B):
+        o_ref, l_ref = oracle.forward(q[b], k[b], v[b], spd[b], table, scale)
+        check_fwd(f"graph {b}", to_np(o[b]), to_np(l[b]), o_ref, l_ref, "bf16")
+        o_in[b], l_in[b] = synth.round_bf16(o_ref.astype(np.float32)), l_ref.astype(np.float32)
+        refs.append(oracle.ring_backward_step(q[b], o_in[b], l_in[b], do[b], k[b], v[b], spd[b], 0, 0, table, scale))
+    got = gt.gt_attn_bwd_batch(Q, K, V, S, T, to_dev(o_in, bf), to_dev(l_in), dO)
+    torch.cuda.synchronize()
+    if N == 1:   # P is 1 and dS the rounding of dO.(V - O): no relative bar
+        return
+    for b, ref in enumerate(refs):
+        check_grads(f"graph {b}", dict(dq=to_np(got[0][b]), dk=to_np(got[1][b]), dv=to_np(got[2][b])),
+                    dict(dq=ref[0], dk=ref[1], dv=ref[2]), "bf16")
+    check_grads("dtable", dict(dtable=to_np(got[3])), dict(dtable=sum(r[3] for r in refs)), "bf16")
