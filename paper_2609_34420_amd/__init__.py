@@ -122,8 +122,9 @@ def _ptr(x) -> int | None:
 
 
 def _stream(stream) -> int | None:
+    # the raw handle of torch.cuda.current_stream(), without the Stream object
     if stream is None:
-        stream = torch.cuda.current_stream()
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     return stream.cuda_stream
 
 
@@ -145,34 +146,46 @@ def _need(cond: bool, msg: str):
 _HEAD_DIMS = (8, 16, 32, 64)
 
 
+# (The checks run on every call, most of the host time of a small one: the
+# messages are formatted only when a check fails.)
 def _shape(t, name: str, shape, dtype=None):
-    _need(isinstance(t, torch.Tensor), f"{name} must be a tensor")
-    _need(tuple(t.shape) == tuple(shape), f"{name} must have shape {tuple(shape)}, got {tuple(t.shape)}")
-    if dtype is not None:
-        _need(t.dtype == dtype, f"{name} must be {dtype}, got {t.dtype}")
+    if not isinstance(t, torch.Tensor):
+        raise ValueError(f"{name} must be a tensor")
+    if t.shape != shape:
+        raise ValueError(f"{name} must have shape {tuple(shape)}, got {tuple(t.shape)}")
+    if dtype is not None and t.dtype != dtype:
+        raise ValueError(f"{name} must be {dtype}, got {t.dtype}")
 
 
 def _qdims(q, name: str, ndim: int):
-    _need(isinstance(q, torch.Tensor) and q.dim() == ndim, f"{name} must be a {ndim}-D tensor")
-    _need(q.dtype in (torch.bfloat16, torch.float32), f"{name} must be bfloat16 or float32, got {q.dtype}")
-    _need(q.shape[-1] in _HEAD_DIMS, f"head dim must be one of {_HEAD_DIMS}, got {q.shape[-1]}")
-    _need(all(n >= 1 for n in q.shape), f"{name} must not be empty")
-    return q.dtype
+    if not isinstance(q, torch.Tensor) or q.dim() != ndim:
+        raise ValueError(f"{name} must be a {ndim}-D tensor")
+    dt = q.dtype
+    if dt != torch.bfloat16 and dt != torch.float32:
+        raise ValueError(f"{name} must be bfloat16 or float32, got {dt}")
+    if q.shape[-1] not in _HEAD_DIMS:
+        raise ValueError(f"head dim must be one of {_HEAD_DIMS}, got {q.shape[-1]}")
+    if q.numel() == 0:
+        raise ValueError(f"{name} must not be empty")
+    return dt
 
 
 def _table(table, H: int):
-    _need(isinstance(table, torch.Tensor) and table.dim() == 2 and table.shape[0] == H
-          and table.dtype == torch.float32, f"table must be fp32 [H={H}, n_buckets]")
-    _need(1 <= table.shape[1] <= 256, f"table must have 1..256 buckets, got {table.shape[1]}")
+    if not (isinstance(table, torch.Tensor) and table.dim() == 2 and table.shape[0] == H
+            and table.dtype == torch.float32):
+        raise ValueError(f"table must be fp32 [H={H}, n_buckets]")
+    if not 1 <= table.shape[1] <= 256:
+        raise ValueError(f"table must have 1..256 buckets, got {table.shape[1]}")
 
 
 def _devices(ref, *ts, contiguous=True):
     """Every tensor is a device tensor on ref's device (and contiguous)."""
     _need(ref.is_cuda, "tensors must be device tensors")
+    dev = ref.get_device()
     for t in ts:
         if t is None:
             continue
-        _need(t.is_cuda and t.device == ref.device, "tensors must be device tensors on one device")
+        _need(t.get_device() == dev, "tensors must be device tensors on one device")
         if contiguous:
             _need(t.is_contiguous(), "tensors must be contiguous")
 
