@@ -61,19 +61,23 @@ constexpr int dkdv_tile_rows() { return D == 64 && QS == 2 ? 64 : (QS == 1 ? 64 
 // kRowsAny: rows of spd on dword boundaries, or at any address, transposed
 // through LDS.
 enum SpdRead { kTrans = 0, kRowsDw = 1, kRowsAny = 2 };
-// Table / histogram copies: lane & (CPY - 1); 32 copies (two lanes per copy)
-// in the 128-bucket layout, else 16.
-template <int NB>
-constexpr int copies() { return NB <= 128 ? 32 : 16; }
 
 // All LDS of the kernel in one block, at LDS address 0: the staged tiles
-// first (their offsets stay inside the reach of the DS immediate), then,
-// from byte 64 KiB, the table copies and right after them the histogram
-// copies. The per-element address register holds the absolute address of
-// the table entry (bucket, copy); the histogram entry is at a fixed
-// immediate offset (ENT * 8) from it. NB (128 or 256) bounds the byte
-// values the layout covers. The statistics and the spd staging lie below the
-// table, or behind the histogram where the tiles take the whole 64 KiB.
+// first (their offsets stay inside the reach of the DS immediate), then the
+// bias table and the gradient histogram in CPY copies (copy = lane mod CPY).
+// NB (128 or 256) bounds the byte values the layout covers.
+//   Paired: the table copies from byte 64 KiB, the histogram copies right
+//   after them at the same 8-byte stride, so that one register addresses both
+//   (the histogram at a fixed immediate offset). 32 copies (two lanes each)
+//   of 128 buckets, or 16 of 256. The statistics and the spd staging lie below
+//   the table, or behind the histogram where the tiles take the whole 64 KiB.
+//   Halved: 256 buckets in 32 copies, where the tiles take at most 32 KiB: the
+//   histogram from byte 64 KiB, the table (4 bytes an entry) from 32 KiB, at
+//   half the histogram's address. The address is one byte permute and the
+//   table's one shift, two operations as in the 16-copy layout, whose four
+//   lanes per copy cost bank conflicts (N = 32768, H = 16, d = 64, 256 buckets:
+//   forward and backward 25.58 ms with 16 copies, 24.44 with 32). Up to 128
+//   buckets pairing stays: it needs no shift and has 32 copies as it is.
 constexpr uint32_t kTabBase = 65536;
 template <int D, int BQ>
 struct DkdvTiles {
@@ -87,28 +91,57 @@ struct DkdvRows {
   float red[3][kNW];
   uint8_t stage[kNW][1024];         // per wave: a 32 x 32 block of spd bytes (row-wise staging)
 };
-template <int NB>
+enum DkdvForm { kPaired = 0, kPairedFull = 1, kHalved = 2 };
+template <int D, int NB, int BQ>
+constexpr DkdvForm dkdv_form() {
+  return NB > 128 && sizeof(DkdvTiles<D, BQ>) <= kTabBase / 2
+             ? kHalved : (sizeof(DkdvTiles<D, BQ>) == kTabBase ? kPairedFull : kPaired);
+}
+template <int NB, DkdvForm F>
 struct DkdvTable {
-  static constexpr int ENT = NB * copies<NB>();   // entry (b, c) = b * CPY + c
+  static constexpr int CPY = NB <= 128 || F == kHalved ? 32 : 16;
+  static constexpr int ENT = NB * CPY;            // entry (b, c) = b * CPY + c
   uint2 tabw[ENT];                  // table copies (fp32 bits, 8-byte stride)
   unsigned long long hist[ENT];     // gradient histogram copies, same index
+  __device__ __forceinline__ void set_table(int t, float v) { tabw[t] = make_uint2(__float_as_uint(v), 0u); }
 };
-template <int D, int NB, int BQ, bool FULL = (sizeof(DkdvTiles<D, BQ>) == kTabBase)>
+template <int NB>
+struct DkdvTable<NB, kHalved> {
+  static constexpr int CPY = 32;
+  static constexpr int ENT = NB * CPY;
+  float tab[ENT];
+  unsigned long long hist[ENT];
+  __device__ __forceinline__ void set_table(int t, float v) { tab[t] = v; }
+};
+template <int D, int NB, int BQ, DkdvForm F = dkdv_form<D, NB, BQ>()>
 struct DkdvSmem : DkdvTiles<D, BQ>, DkdvRows<BQ> {
   uint8_t pad[kTabBase - sizeof(DkdvTiles<D, BQ>) - sizeof(DkdvRows<BQ>)];
-  DkdvTable<NB> t;
+  DkdvTable<NB, F> t;
 };
 template <int D, int NB, int BQ>
-struct DkdvSmem<D, NB, BQ, true> : DkdvTiles<D, BQ> {
-  DkdvTable<NB> t;
+struct DkdvSmem<D, NB, BQ, kPairedFull> : DkdvTiles<D, BQ> {
+  DkdvTable<NB, kPairedFull> t;
   DkdvRows<BQ> r;
 };
-template <int D, int NB, int BQ, bool FULL>
-__device__ __forceinline__ DkdvRows<BQ>& rows_of(DkdvSmem<D, NB, BQ, FULL>& sm) {
-  if constexpr (FULL)
-    return sm.r;
-  else
+// tiles at most 32 KiB, then padding up to the table
+template <int D, int NB, int BQ>
+struct DkdvSmem<D, NB, BQ, kHalved> {
+  union {
+    uint8_t front[kTabBase / 2];
+    struct {
+      uint16_t q[2][BQ * D];
+      uint16_t o[2][BQ * D];
+    };
+  };
+  DkdvTable<NB, kHalved> t;
+  DkdvRows<BQ> r;
+};
+template <int D, int NB, int BQ, DkdvForm F>
+__device__ __forceinline__ DkdvRows<BQ>& rows_of(DkdvSmem<D, NB, BQ, F>& sm) {
+  if constexpr (F == kPaired)
     return sm;
+  else
+    return sm.r;
 }
 
 // Per-lane LDS element offsets of the operand reads (tile-relative; the
@@ -229,11 +262,14 @@ __device__ __forceinline__ void dkdv_subblock(DkdvSmem<D, NB, BQ>& sm, const Dkd
   // Lane: key; registers r: queries. dp holds (dO.V - Dlt) 2^F, so ds below
   // is dS 2^F.
   float p[16], ds[16];
-  uint32_t addr[16];   // absolute LDS address of table entry (bucket, copy)
+  uint32_t addr[16];   // absolute LDS address of entry (bucket, copy): of the table, halved: of the histogram
   float tb[16];
-  constexpr int CPY = copies<NB>();
+  constexpr DkdvForm FORM = dkdv_form<D, NB, BQ>();
+  using Table = DkdvTable<NB, FORM>;
+  constexpr int CPY = Table::CPY;
   // copy offset with the table base: kTabBase = 1 << 16 is byte 2, so a
-  // byte permute can put the bucket into byte 1 and keep both
+  // byte permute can put the bucket into byte 1 and keep both. Halved, it is
+  // the histogram that starts there.
   const uint32_t cpyb = (uint32_t)(lane & (CPY - 1)) * 8u | kTabBase;
   uint32_t w[4];
   if constexpr (READ != kTrans) {
@@ -268,7 +304,7 @@ __device__ __forceinline__ void dkdv_subblock(DkdvSmem<D, NB, BQ>& sm, const Dkd
   const uint8_t* lds0 = reinterpret_cast<const uint8_t*>(&sm);
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
-    tb[r] = *reinterpret_cast<const float*>(lds0 + addr[r]);
+    tb[r] = *reinterpret_cast<const float*>(lds0 + (FORM == kHalved ? addr[r] >> 1 : addr[r]));
   }
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
@@ -278,7 +314,7 @@ __device__ __forceinline__ void dkdv_subblock(DkdvSmem<D, NB, BQ>& sm, const Dkd
     p[r] = pv;
     ds[r] = pv * dp[r];
   }
-  constexpr uint32_t kHistOff = DkdvTable<NB>::ENT * 8;
+  constexpr uint32_t kHistOff = FORM == kHalved ? 0u : Table::ENT * 8;
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
     unsigned long long* hp = reinterpret_cast<unsigned long long*>(const_cast<uint8_t*>(lds0) + addr[r] + kHistOff);
@@ -436,9 +472,10 @@ __device__ __forceinline__ void dkdv_main(const BwdArgs& a, DkdvSmem<D, NB, BQ>&
 
   if constexpr (QS > 1) {
     // group qs + half's dK and dV are added to group qs's through the LDS
-    // below the table (the last step's barrier has ended every read of it)
+    // below 64 KiB: the tiles and, halved, the table (the last step's barrier
+    // has ended every read of both)
     constexpr int XW = 2 * NCB * 16 * 64;      // floats of one wave's accumulators
-    static_assert(XW * 4 * kNW / 2 <= (int)kTabBase, "the exchange fits below the table");
+    static_assert(XW * 4 * kNW / 2 <= (int)kTabBase, "the exchange ends below the histogram");
     float* xbuf = reinterpret_cast<float*>(&sm);
 #pragma unroll
     for (int half = QS / 2; half >= 1; half /= 2) {
@@ -515,11 +552,12 @@ __device__ __forceinline__ void dkdv_main(const BwdArgs& a, DkdvSmem<D, NB, BQ>&
 // (8 and 16 run on 32-wide tiles whose extra features are zero).
 template <int D, int DS, int NB, int QS, SpdRead READ>
 __global__ __launch_bounds__(kThreads, 2) void bwd_dkdv_bf16_kernel(BwdArgs a) {
-  constexpr int CPY = copies<NB>();
   constexpr int kBK = kNW / QS * 32;           // keys per workgroup
   using Smem = DkdvSmem<D, NB, dkdv_tile_rows<D, QS>()>;
+  using Table = DkdvTable<NB, dkdv_form<D, NB, dkdv_tile_rows<D, QS>()>()>;
+  constexpr int CPY = Table::CPY;
   __shared__ __attribute__((aligned(16))) Smem sm;
-  uint2* tabw = sm.t.tabw;
+  static_assert(offsetof(Smem, t) == (CPY == 32 && NB > 128 ? kTabBase / 2 : kTabBase), "table base");
   unsigned long long* hist = sm.t.hist;
   float (*red)[kNW] = rows_of(sm).red;
   const int tid = threadIdx.x;
@@ -531,10 +569,10 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dkdv_bf16_kernel(BwdArgs a) {
   const int64_t j = kblk * kBK + (QS == 1 ? wave : wave % (kNW / QS)) * 32 + col;
   const bool jok = j < a.Sk;
 
-  for (int t = tid; t < DkdvTable<NB>::ENT; t += kThreads) {
+  for (int t = tid; t < Table::ENT; t += kThreads) {
     const int bkt = t / CPY;
     const float tv = (bkt < a.n_buckets) ? a.table[(int64_t)table_row(a, h) * a.n_buckets + bkt] * kLog2e : 0.0f;
-    tabw[t] = make_uint2(__float_as_uint(tv), 0u);
+    sm.t.set_table(t, tv);
     hist[t] = 0ull;
   }
 

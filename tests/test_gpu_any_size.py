@@ -96,6 +96,18 @@ def test_any_size_bf16(H, Sq, Sk, d, first, pad, nb):
     run_case("bf16", H, Sq, Sk, d, first, pad, nb)
 
 
+# More than 127 buckets in dK/dV: each split of the waves with each of its two
+# LDS layouts (d = 64: the four-way split keeps 16 table copies, the others
+# have 32), the largest byte value, and bytes past the last bucket.
+@pytest.mark.parametrize("H,Sq,Sk,d,first,pad,nb", [
+    (1, 130, 300, 64, 0, 0, 256), (1, 130, 300, 32, 1, 0, 256), (1, 70, 100, 8, 0, 0, 128),
+    (128, 300, 300, 64, 0, 0, 256), (128, 300, 301, 32, 1, 2, 255), (256, 300, 299, 64, 0, 0, 128),
+    (256, 256, 512, 64, 0, 0, 256), (256, 300, 300, 16, 8, 4, 200),
+])
+def test_many_buckets_bf16(H, Sq, Sk, d, first, pad, nb):
+    run_case("bf16", H, Sq, Sk, d, first, pad, nb)
+
+
 @pytest.mark.parametrize("H,Sq,Sk,d,first,pad,nb", CASES)
 def test_any_size_f32(H, Sq, Sk, d, first, pad, nb):
     run_case("f32", H, Sq, Sk, d, first, pad, nb)
