@@ -10,7 +10,7 @@ HBM), bias table [8, 64].
 
 Other workloads (--workload):
   ba16k    N = 16384, H = 8, d = 64, bf16, Barabasi-Albert spd, 32 buckets
-  tiny     N = 512, H = 4, d = 32, fp32 (vector-ALU kernels), 22 buckets
+  tiny     N = 512, H = 4, d = 32, fp32 (fp32 matrix cores), 22 buckets
   cp256k   one device's share of the context-parallel ring at N = 262144:
            query shard 3 of 8 (32768 rows, with only its spd rows) against
            the 8 KV blocks in ring order, merged in place; the step is the
@@ -46,7 +46,7 @@ ROOT = Path(__file__).resolve().parent
 sys.path.insert(0, str(ROOT))
 
 PEAK_BF16 = 2516.6e12        # MI355X dense bf16 matrix-core FLOP/s
-PEAK_F32_VALU = 157.3e12     # MI355X fp32 vector FLOP/s
+PEAK_F32 = 157.3e12          # MI355X fp32 matrix (and vector) FLOP/s
 PEAK_HBM = 8.0e12            # MI355X HBM3E bytes/s
 WORKLOADS = ("sbm128k", "ba16k", "tiny", "cp256k", "deep32k")
 
@@ -219,8 +219,8 @@ def dtable_spread(runs):
 # The kernel symbol behind each timed launch name.
 KERNEL_SYMBOLS = {"fwd": "fwd_bf16_kernel", "fwd_ring_step": "fwd_bf16_kernel",
                   "bwd_prep": "bwd_prep_kernel", "bwd_dkdv": "bwd_dkdv_bf16_kernel",
-                  "bwd_dq": "bwd_dq_bf16_kernel", "fwd_valu": "fwd_valu_kernel",
-                  "bwd_dkdv_valu": "bwd_dkdv_valu_kernel", "bwd_dq_valu": "bwd_dq_valu_kernel"}
+                  "bwd_dq": "bwd_dq_bf16_kernel", "fwd_f32": "fwd_f32_kernel",
+                  "bwd_dkdv_f32": "bwd_dkdv_f32_kernel", "bwd_dq_f32": "bwd_dq_f32_kernel"}
 
 
 def measured_traffic(workload: str, kernel: str):
@@ -278,9 +278,9 @@ def run_layer(w, args, dev):
     # BFS distances on an undirected graph are symmetric: spd is its own
     # transpose, which lets the key-stationary stage read rows.
     spd_t = spd if w.spd_symmetric else None
-    names = ("bwd_prep", "bwd_dkdv", "bwd_dq") if w.dtype == "bf16" else ("bwd_prep", "bwd_dkdv_valu",
-                                                                         "bwd_dq_valu")
-    fname = "fwd" if w.dtype == "bf16" else "fwd_valu"
+    names = ("bwd_prep", "bwd_dkdv", "bwd_dq") if w.dtype == "bf16" else ("bwd_prep", "bwd_dkdv_f32",
+                                                                         "bwd_dq_f32")
+    fname = "fwd" if w.dtype == "bf16" else "fwd_f32"
 
     def step(t):
         if t: t.mark(fname)
@@ -612,7 +612,7 @@ def metric_of(w) -> str:
     if w.layers > 1:
         return (f"{w.layers}-layer biased-attention fwd+bwd TFLOP/s and % bf16 MFMA peak at N={w.N}, "
                 f"H={w.H}, d={w.d}")
-    prec = "bf16 MFMA" if w.dtype == "bf16" else "fp32 vector"
+    prec = "bf16 MFMA" if w.dtype == "bf16" else "fp32 matrix"
     return f"biased-attention fwd+bwd TFLOP/s and % {prec} peak at N={w.N}, H={w.H}, d={w.d}"
 
 
@@ -643,7 +643,7 @@ def main():
     K = args.steps
     ms = sum(r["steps"]) / len(r["steps"])
     tflops = r["flop_per_step"] / (ms * 1e-3) / 1e12
-    peak = PEAK_BF16 if w.dtype == "bf16" else PEAK_F32_VALU
+    peak = PEAK_BF16 if w.dtype == "bf16" else PEAK_F32
 
     # dominant kernel: the largest share of the step
     share = {n: r["per_launch"][n] * r["launches"][n] for n in r["per_launch"] if n in r["flops"]}

@@ -114,7 +114,7 @@ size_t gt_attn_bwd_workspace_size(int32_t H, int64_t N, int32_t d, gt_dtype_t dt
  *            symmetric: pass spd itself. A directed graph's spd is fixed per
  *            graph, so its transpose can be built once. NULL, or a spd_t
  *            that is not 16-byte aligned or with N not a multiple of 16, is
- *            ignored (columns of spd are gathered). A spd_t that is not the
+ *            ignored (rows of spd are read and transposed). A spd_t that is not the
  *            transpose of spd gives wrong dK, dV and dtable.
  *   o, lse   the forward outputs for the same inputs
  *   d_o      [H, N, d] dtype

@@ -10,10 +10,10 @@
 // dP from -Dlt, so per score element the vector work is one FMA with the
 // bias, one exp2, one multiply and the two bf16 conversions.
 //
-// Bias and table gradient: the table (times log2 e) is replicated in LDS
-// (copy = lane & 31 when there are at most 128 buckets, else lane & 15) and
-// the bucket histogram has the same layout, so
-// one address register serves the bias read and the gradient add. The
+// Bias and table gradient: the table (times log2 e) and the bucket histogram
+// are replicated in LDS (copy = lane & 31, or lane & 15 for more than 128
+// buckets where the tiles leave no room for 32 copies), laid out so that one
+// address per element serves the bias read and the gradient add (DkdvForm). The
 // histogram is fixed point: LDS float atomics are slow on this hardware,
 // 64-bit integer adds are not. dS is accumulated as round(dS * 2^F), where
 // the power-of-two scale per head keeps every term below 2^30 in magnitude:

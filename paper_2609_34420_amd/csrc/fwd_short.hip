@@ -1,4 +1,4 @@
-// Persistent forward for short sequences (bf16, head dims up to 32): see the
+// Persistent forward for short sequences (bf16, every head dim): see the
 // kernel's description below. The building blocks are those of the full
 // forward (fwd_tile.hpp).
 #include "common.hpp"
@@ -192,10 +192,10 @@ __device__ __forceinline__ void softmax_first(const f32x16& s, const bf16x8 (&vo
 }
 
 // Persistent forward for sequences of at most 256 rows with at most 127
-// buckets (bf16 in and out, head dims 8, 16, 32 on 32-wide tiles). Each wave owns 32 queries, and the
-// sequence's K and V (all rows) sit in LDS: one pair of barriers per
-// sequence instead of one barrier per key tile. At N > 128 a workgroup
-// covers one sequence; shorter ones are packed, 2, 4 or 8 sequences of the
+// buckets (bf16 in and out, head dims 8, 16, 32 on 32-wide tiles, 64 on its
+// own). Each wave owns 32 queries, and the sequence's K and V (all rows) sit
+// in LDS: one pair of barriers per sequence instead of one barrier per key
+// tile. At N > 128 a workgroup covers one sequence; shorter ones are packed, 2, 4 or 8 sequences of the
 // head at once (N <= 128, 64, 32), each in its own slice of the K and V
 // rows with 4, 2 or 1 waves. The per-lane bias table holds the byte values
 // 0..127 (bytes of 128 or more are mapped to the padding entry 127, bias 0)
