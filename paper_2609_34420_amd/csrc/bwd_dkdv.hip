@@ -385,13 +385,18 @@ __device__ __forceinline__ void dkdv_main(const BwdArgs& a, DkdvSmem<D, NB, BQ>&
   const DkdvOffsets<D> off(row0);
 
   // Bucket indices of this lane's key. kTrans: 16 queries as one 16-byte row
-  // segment of spd_t (rows of this key block only; past the block's last row
-  // a load reads zeros). Else lane l loads row l / 2 of the sub-block, bytes
-  // 16 (l % 2) .. + 15 of the wave's 32 keys, through a resource that starts
-  // at the sub-block's first row and ends with the last query row's last key
-  // (rows past Sq read zero, a sub-block past Sq reads the last one; their P is
-  // 0). The sub-block's first row is a multiple of 32, so the lane's address
-  // mod 16 is the same for every sub-block.
+  // segment of spd_t (N a multiple of 16), which at a row's end may lie past
+  // it. A whole key block is followed by another one's rows, or ends the matrix
+  // at an N that is a multiple of BK, and so of BQ where BQ <= BK (else the
+  // offset is clamped to the row's last 32): its loads are inside spd_t. In the
+  // partial block a load past its last row reads zeros. (Headline shape, whole
+  // blocks with the offset in the lane too: 191.2 ms a step, 189.5 without.)
+  // Else lane l loads row l / 2 of the sub-block, bytes 16 (l % 2) .. + 15 of
+  // the wave's 32 keys, through a resource that starts at the sub-block's first
+  // row and ends with the last query row's last key (rows past Sq read zero, a
+  // sub-block past Sq reads the last one; their P is 0). The sub-block's first
+  // row is a multiple of 32, so the lane's address mod 16 is the same for every
+  // sub-block.
   constexpr int BK = NKW * 32;
   constexpr int NBT = READ == kRowsAny ? 5 : 4;
   const __amdgpu_buffer_rsrc_t rs_t =
@@ -414,16 +419,19 @@ __device__ __forceinline__ void dkdv_main(const BwdArgs& a, DkdvSmem<D, NB, BQ>&
   const int64_t last32 = (a.Sq - 1) & ~(int64_t)31;
   auto fetch = [&](int64_t i_base, uint32_t (&dst)[NBT]) {
     if constexpr (READ == kTrans) {
-      buf_u128(rs_t, voff, (uint32_t)i_base, dst);
+      if constexpr (!KTAIL)
+        buf_u128_inside(rs_t, voff, (uint32_t)(BQ > BK && i_base > last32 ? last32 : i_base), dst);
+      else
+        buf_u128(rs_t, voff + (uint32_t)i_base, dst);
     } else {
       const int64_t ib = i_base < last32 ? i_base : last32;
       uint32_t rem;
       const __amdgpu_buffer_rsrc_t rs =
           spd_rsrc<READ == kRowsAny>(spd_cols + ib * ld, (a.Sq - 1 - ib) * ld + (a.Sk - key0), rem);
       if constexpr (READ == kRowsAny)
-        load_spd5(rs, voff, 0u, dst);
+        load_spd5(rs, voff, dst);
       else
-        buf_u128(rs, voff, 0u, dst);
+        buf_u128(rs, voff, dst);
     }
   };
 

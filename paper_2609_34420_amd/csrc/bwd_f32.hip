@@ -283,7 +283,7 @@ __global__ __launch_bounds__(kThreadsF, 1) void bwd_dkdv_f32_kernel(BwdArgs a) {
   auto fetch = [&](int64_t i_base, uint32_t (&w)[5]) {
     const int64_t ib = i_base < last32 ? i_base : last32;
     uint32_t rem;
-    load_spd5(spd_rsrc<true>(spd_cols + ib * ld, (a.Sq - 1 - ib) * ld + (a.Sk - kc), rem), voff, 0u, w);
+    load_spd5(spd_rsrc<true>(spd_cols + ib * ld, (a.Sq - 1 - ib) * ld + (a.Sk - kc), rem), voff, w);
   };
   int off_tr8[2];
 #pragma unroll

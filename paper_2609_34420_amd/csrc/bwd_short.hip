@@ -407,20 +407,21 @@ __global__ __launch_bounds__(kThreads, 1) void bwd_short_bf16_kernel(BwdArgs a) 
   auto fetch = [&](int s, int qb, uint32_t (&dst)[NBT]) {
     const int h = s * a.hpb + head;
     if constexpr (READ == kTrans) {
-      const __amdgpu_buffer_rsrc_t rs = make_rsrc_n(seq_spd_t(a, h), (int64_t)N * ld);
-      buf_u128(rs, (uint32_t)(jc * ld + 16 * g), (uint32_t)(qb * 32), dst);
+      const __amdgpu_buffer_rsrc_t rs = make_rsrc_from(seq_spd_t(a, h), N * ld, qb * 32);
+      buf_u128(rs, (uint32_t)(jc * ld + 16 * g), dst);
     } else {
       uint32_t rem;
-      const __amdgpu_buffer_rsrc_t rs = spd_rsrc<READ == kRowsAny>(seq_spd(a, h), (int64_t)(N - 1) * ld + N, rem);
+      const __amdgpu_buffer_rsrc_t rs = spd_rsrc<READ == kRowsAny>(seq_spd(a, h), (int64_t)(N - 1) * ld + N, rem,
+                                                                         qb * 32 * ld);
       if constexpr (READ == kRowsAny) {
         const uint32_t v = voff_st + rem;
         uint32_t w5[5];
-        load_spd5(rs, v & ~3u, (uint32_t)(qb * 32 * ld), w5);
+        load_spd5(rs, v & ~3u, w5);
 #pragma unroll
         for (int u = 0; u < 5; ++u) dst[u] = w5[u];
         dst[5] = v & 3u;
       } else {
-        buf_u128(rs, voff_st, (uint32_t)(qb * 32 * ld), dst);
+        buf_u128(rs, voff_st, dst);
       }
     }
   };

@@ -143,30 +143,41 @@ __device__ __forceinline__ int64_t xcd_remap(int64_t w, int64_t total) {
 }
 
 // Raw buffer resource over [base, base + 2 GiB): untyped loads, 32-bit data
-// format (the gfx9-family descriptor word). Offsets passed to the loads below
-// are always inside the caller's buffer; the range field is not relied on.
+// format (the gfx9-family descriptor word). Its loads are always inside the
+// caller's buffer; the range field is not relied on.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, 0x7fffffff, 0x00020000);
 }
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ void buf_u128(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff,
-                                         uint32_t w[4]) {
+// Range check of a raw buffer load: only the lane offset (with the
+// instruction's immediate) is counted on to be compared with the resource's
+// end. A scalar offset is documented as left out of the comparison, and as
+// subtracted from the end, which then goes negative for one past it; so where a
+// load may lie past the end, the scalar part goes into the resource's start
+// (make_rsrc_from in stage.hpp), and a scalar offset is given only to loads that are
+// always inside.
+__device__ __forceinline__ void buf_u128(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t w[4]) {
+  const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, voff, 0, 0);
+  w[0] = v[0]; w[1] = v[1]; w[2] = v[2]; w[3] = v[3];
+}
+// Of a load that is inside the caller's buffer whatever the lane.
+__device__ __forceinline__ void buf_u128_inside(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff,
+                                                uint32_t w[4]) {
   const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0);
   w[0] = v[0]; w[1] = v[1]; w[2] = v[2]; w[3] = v[3];
 }
 
-// A 16-byte spd group at any byte address, as the 5 dwords that hold it (voff4
-// + soff: its address rounded down to a dword; dwords past the resource's end
+// A 16-byte spd group at any byte address, as the 5 dwords that hold it
+// (voff4: its offset rounded down to a dword; dwords past the resource's end
 // read 0). A load of 16 bytes from an odd address costs up to 1.4 times the
 // whole forward (N = 16001 against 16004 at H = 8, d = 64: 936 and 659 us),
 // one from a dword boundary costs no more than an aligned one.
-__device__ __forceinline__ void load_spd5(__amdgpu_buffer_rsrc_t r, uint32_t voff4, uint32_t soff,
-                                          uint32_t (&w)[5]) {
-  const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, voff4, soff, 0);
+__device__ __forceinline__ void load_spd5(__amdgpu_buffer_rsrc_t r, uint32_t voff4, uint32_t (&w)[5]) {
+  const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, voff4, 0, 0);
   w[0] = v[0]; w[1] = v[1]; w[2] = v[2]; w[3] = v[3];
-  w[4] = __builtin_amdgcn_raw_buffer_load_b32(r, voff4, soff + 16u, 0);
+  w[4] = __builtin_amdgcn_raw_buffer_load_b32(r, voff4 + 16u, 0, 0);
 }
 // Its 16 bytes into w[0..3] (sh: its address mod 4).
 __device__ __forceinline__ void align_spd5(uint32_t (&w)[5], uint32_t sh) {

@@ -333,18 +333,21 @@ __global__ __launch_bounds__(kThreads, DS <= 16 ? 4 : 2) void fwd_short_bf16_ker
                                         : zero_bf16x8();
     }
   };
+  // sequence s's matrix
   auto spd_rs = [&](int s, uint32_t& rem) {
     const int h = s * a.hpb + head;
     return spd_rsrc<ANY>(seq_spd(a, h), (int64_t)(N - 1) * ld + N, rem);
   };
   const uint32_t voff = (uint32_t)(qc * ld + 16 * g);
   // Words of the key block at byte j of the lane's row (ANY: at any address,
-  // as the 5 dwords that hold them).
+  // as the 5 dwords that hold them; a whole last block: all of them inside).
   auto spd_load = [&](const __amdgpu_buffer_rsrc_t& r, uint32_t rem, uint32_t j, uint32_t (&w)[NWD]) {
     if constexpr (ANY)
-      load_spd5(r, (voff + rem) & ~3u, j, w);
+      load_spd5(r, ((voff + rem) & ~3u) + j, w);
+    else if constexpr (TAIL)
+      buf_u128(r, voff + j, w);
     else
-      buf_u128(r, voff, j, w);
+      buf_u128_inside(r, voff, j, w);
   };
   // Bucket words of key block kb as table entries: bytes of 128 or more to
   // the padding entry 127; with TAIL, keys past N to the -inf entry.

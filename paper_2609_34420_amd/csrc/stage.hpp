@@ -36,9 +36,17 @@ __device__ __forceinline__ int swz_tile(int row, int chunk) {
 }
 
 // Raw buffer resource over exactly nbytes: loads past the end return 0.
+__device__ __forceinline__ int rsrc_range(int64_t nbytes) {
+  return (int)(nbytes < 0x7fffffff ? nbytes : 0x7fffffff);
+}
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc_n(const void* base, int64_t nbytes) {
-  const int n = (int)(nbytes < 0x7fffffff ? nbytes : 0x7fffffff);
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, n, 0x00020000);
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, rsrc_range(nbytes), 0x00020000);
+}
+// The same of `range` bytes from `start` bytes on, with the same end: empty if
+// start is past it.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc_from(const uint8_t* base, int range, int start) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(base) + start, (short)0,
+                                           range > start ? range - start : 0, 0x00020000);
 }
 
 // Resource over rows [r0, min(r0 + ROWS, nrows)) of a row-major [nrows, D]
@@ -245,11 +253,17 @@ __device__ __forceinline__ void load_bias(const float* tab, const uint32_t (&w)[
 // byte's dword: reads through it never touch a dword that holds no byte of
 // them (past the end they return 0, dword by dword). ANY: p may be any
 // address; the resource then starts at the 16-byte boundary below it and rem
-// is the distance to p. Otherwise p is on a dword boundary.
+// is the distance to p. Otherwise p is on a dword boundary. With start
+// (wave-uniform, a multiple of 16): make_rsrc_from.
 template <bool ANY>
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t spd_rsrc(const uint8_t* p, int64_t bytes, uint32_t& rem) {
   rem = ANY ? (uint32_t)(reinterpret_cast<uintptr_t>(p) & 15u) : 0u;
   return make_rsrc_n(p - rem, (bytes + rem + 3) & ~(int64_t)3);
+}
+template <bool ANY>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t spd_rsrc(const uint8_t* p, int64_t bytes, uint32_t& rem, int start) {
+  rem = ANY ? (uint32_t)(reinterpret_cast<uintptr_t>(p) & 15u) : 0u;
+  return make_rsrc_from(p - rem, rsrc_range((bytes + rem + 3) & ~(int64_t)3), start);
 }
 
 // Sizes and spd alignment a query-stationary kernel takes. kWhole: the query
@@ -263,8 +277,9 @@ enum SpdRows { kWhole = 0, kRagged = 1, kBytes = 2 };
 // The spd words a wave of a query-stationary kernel streams: for the lane's
 // query rows, groups of 16 keys (lane half g: keys 16 g .. + 15 of each 32-key
 // block kb) of the wave's part (from key `part` on) of every TR-key tile, by
-// raw buffer loads: scalar base per wave, lane offset row * ld + 16 g, scalar
-// key offset.
+// raw buffer loads: a resource per wave and tile that starts at the part's first
+// key (kWhole: per wave, with a scalar key offset), lane offset row * ld + 16 g
+// + 32 kb.
 template <SpdRows ROWS, int TR>
 struct SpdStream {
   static constexpr bool BYTES = ROWS == kBytes;
@@ -272,16 +287,18 @@ struct SpdStream {
   static constexpr int OPS = BYTES ? 2 : 1;          // vector-memory ops per group
   struct Row { uint32_t voff, sh; };                 // a lane's row: offset, its address mod 4 (kBytes)
 
-  uint32_t rem = 0;
-  __amdgpu_buffer_rsrc_t rs;
+  uint32_t rem;                                      // kBytes: the first row's address mod 16
+  const uint8_t* base;                               // the first row, or the 16-byte boundary below it
+  int range;                                         // bytes from there to the end of the last key's dword
+  __amdgpu_buffer_rsrc_t rs;                         // kWhole: from the first row on
   int64_t ntiles;
   int part, g16;
 
   // row0: spd of the wave's first row and the block's first key; bytes: from
   // there to the last query row's last key.
   __device__ __forceinline__ SpdStream(const uint8_t* row0, int64_t bytes, int64_t Sk, int part_, int g)
-      : rs(ROWS == kWhole ? make_rsrc(row0) : spd_rsrc<BYTES>(row0, bytes, rem)), ntiles((Sk + TR - 1) / TR),
-        part(part_), g16(16 * g) {}
+      : rem(BYTES ? (uint32_t)(reinterpret_cast<uintptr_t>(row0) & 15u) : 0u), base(row0 - rem),
+        range(rsrc_range((bytes + rem + 3) & ~(int64_t)3)), rs(make_rsrc(row0)), ntiles((Sk + TR - 1) / TR), part(part_), g16(16 * g) {}
   __device__ __forceinline__ Row row(int64_t bytes) const {    // bytes: from the wave's first row
     Row r;
     r.voff = (uint32_t)bytes + (uint32_t)g16 + rem;
@@ -291,11 +308,13 @@ struct SpdStream {
   }
   // Words of group kb of tile tt (clamped to the last).
   __device__ __forceinline__ void fetch(int64_t tt, const Row& r, int kb, uint32_t (&w)[NWD]) const {
-    const int jt = (int)((tt < ntiles ? tt : ntiles - 1) * TR) + part + kb * 32;
-    if constexpr (BYTES)
-      load_spd5(rs, r.voff, (uint32_t)jt, w);
+    const int jt = (int)((tt < ntiles ? tt : ntiles - 1) * TR) + part;
+    if constexpr (ROWS == kWhole)      // whole tiles: every load is inside
+      buf_u128_inside(rs, r.voff, (uint32_t)(jt + kb * 32), w);
+    else if constexpr (BYTES)
+      load_spd5(make_rsrc_from(base, range, jt), r.voff + (uint32_t)(kb * 32), w);
     else
-      buf_u128(rs, r.voff, (uint32_t)jt, w);
+      buf_u128(make_rsrc_from(base, range, jt), r.voff + (uint32_t)(kb * 32), w);
   }
   // Its words moved into w[0..3].
   __device__ __forceinline__ void ready(const Row& r, uint32_t (&w)[NWD]) const {

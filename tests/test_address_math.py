@@ -151,3 +151,133 @@ def test_spd_groups_at_any_address(Sk, addr):
         assert w[:n] == row[j:j + n]
         if addr % 4 == 0:
             assert dwords(a, 4)[:n] == row[j:j + n]
+
+
+def _raw_loads(text):
+    """(function, scalar offset) of every raw buffer load in a source."""
+    out = []
+    for m in re.finditer(r"__builtin_amdgcn_raw_buffer_load_\w+\(", text):
+        depth, i, args, start = 1, m.end(), [], m.end()
+        while depth:
+            c = text[i]
+            if c in "([{":
+                depth += 1
+            elif c in ")]}":
+                depth -= 1
+            if (c == "," and depth == 1) or depth == 0:
+                args.append(text[start:i].strip())
+                start = i + 1
+            i += 1
+        fn = re.findall(r"__forceinline__ \S+ (\w+)\(", text[:m.start()])
+        out.append((fn[-1] if fn else "", args[2]))
+    return out
+
+
+def test_loads_that_may_pass_the_end_have_no_scalar_offset():
+    """A scalar offset is not part of a raw buffer load's range check (or is
+    subtracted from the end, which then goes negative), so only loads that are
+    inside whatever the lane have one: those of buf_u128_inside, taken by the
+    query-stationary kernels on whole tiles, by the short forward on whole key
+    blocks and by dK/dV with a transpose on whole key blocks."""
+    callers = []
+    for f in sorted(CSRC.iterdir()):
+        if f.suffix not in (".hip", ".hpp"):
+            continue
+        text = f.read_text()
+        for fn, soff in _raw_loads(text):
+            assert soff in ("0", "0u") or fn == "buf_u128_inside", (f.name, fn, soff)
+        for m in re.finditer(r"(if constexpr \([^\n]*?\)|else)\s*(//[^\n]*)?\n\s*buf_u128_inside\(", text):
+            callers.append((f.name, m.group(1)))
+        assert text.count("buf_u128_inside(") == (f.name == "common.hpp") + sum(c[0] == f.name for c in callers)
+    assert callers == [("bwd_dkdv.hip", "if constexpr (!KTAIL)"), ("fwd_short.hip", "else"),
+                       ("stage.hpp", "if constexpr (ROWS == kWhole)")]
+    text = (CSRC / "fwd_short.hip").read_text()
+    assert re.search(r"else if constexpr \(TAIL\)\n\s*buf_u128\(.*\n\s*else\n\s*buf_u128_inside", text)
+
+
+# (first row's address, rows of the wave from its first on, keys, row stride,
+# tile, the groups' parts)
+@pytest.mark.parametrize("Sk", [1, 5, 17, 33, 100, 200, 257])
+@pytest.mark.parametrize("rows,pad,addr", [(1, 0, 0), (1, 0, 3), (2, 3, 5), (3, 4, 8), (64, 1, 13)])
+@pytest.mark.parametrize("tile,parts", [(64, (0,)), (128, (0, 32, 64, 96)), (256, (0, 64, 128, 192))])
+def test_query_stationary_spd_reads_stay_in_the_matrix(Sk, rows, pad, addr, tile, parts):
+    """Forward and dQ: the load of a 16-key group whose first key may lie past
+    the last one, or be none of the wave's rows. Its resource starts at the
+    group's key (from the 16-byte boundary below the first row on) and ends
+    with the dword of the last row's last key, empty past it; only the lane
+    offset is compared with that end. No dword past the end is touched and the
+    keys that exist arrive in place."""
+    ld = Sk + pad
+    rem = addr & 15
+    end = (rem + (rows - 1) * ld + Sk + 3) & ~3          # from the boundary on
+    for t in range((Sk + tile - 1) // tile):
+        for part in parts:
+            for kb in range(0, tile // len(parts), 32):
+                skip = t * tile + part + kb
+                records = max(0, end - skip)
+                for row in {0, rows - 1}:
+                    for g in (0, 1):
+                        v = row * ld + 16 * g + rem
+                        sh = v & 3
+                        touched = [skip + v - sh + 4 * i for i in range(5) if v - sh + 4 * i + 4 <= records]
+                        assert all(0 <= x and x + 4 <= end for x in touched)
+                        got = {x + i for x in touched for i in range(4)}
+                        first = skip + 16 * g
+                        for j in range(first, min(first + 16, Sk)):
+                            assert rem + row * ld + j in got
+
+
+@pytest.mark.parametrize("N", list(range(1, 70)) + [96, 100, 130, 200, 224, 255, 256])
+def test_short_spd_reads_stay_in_the_matrix(N):
+    """Short forward (key block j of the lane's row, at least two blocks) and
+    short backward (query block qb of every wave slot, also past the last
+    block): as above, with the whole offset in the lane and with the block's
+    rows in the resource's start."""
+    lgp = 0 if N > 128 else (1 if N > 64 else (2 if N > 32 else 3))
+    for rem in (0, 1, 4, 15):
+        end = (rem + (N - 1) * N + N + 3) & ~3
+        for j in range(0, 32 * max(2, (N + 31) // 32), 32):
+            for row in (0, N // 2, N - 1):
+                for g in (0, 1):
+                    v = (row * N + 16 * g + rem & ~3) + j
+                    touched = [v + 4 * i for i in range(5) if v + 4 * i + 4 <= end]
+                    need = {rem + row * N + k for k in range(j + 16 * g, min(j + 16 * g + 16, N))}
+                    assert need <= {x + i for x in touched for i in range(4)}
+        for qb in range(8 >> lgp):
+            skip = qb * 32 * N
+            assert skip % 16 == 0
+            records = max(0, end - skip)
+            for lane in (0, 1, 31, 62, 63):
+                for wl in range(8 >> lgp):
+                    v = (lane >> 1) * N + 16 * (lane & 1) + wl * 32 + rem & ~3
+                    touched = [skip + v + 4 * i for i in range(5) if v + 4 * i + 4 <= records]
+                    assert all(x + 4 <= end for x in touched)
+                    i = qb * 32 + (lane >> 1)
+                    first = wl * 32 + 16 * (lane & 1)
+                    if i < N:
+                        need = {rem + i * N + k for k in range(first, min(first + 16, N))}
+                        assert need <= {x + b for x in touched for b in range(4)}
+
+
+@pytest.mark.parametrize("N", list(range(16, 700, 16)) + [1008, 1024, 1040, 4096, 4112])
+def test_transposed_spd_reads_stay_in_the_matrix(N):
+    """dK/dV with spd_t (N a multiple of 16): a whole key block's loads are
+    inside the matrix by themselves (the resource ends with the block, but is
+    not relied on); the partial block's are held by the lane offset."""
+    for split, tile in ((1, 64), (2, 64), (2, 128), (4, 128)):
+        bk, nsub = 256 // split, tile // (32 * split)
+        last32, ntiles = (N - 1) & ~31, (N + tile - 1) // tile
+        starts = {t * tile + qs * nsub * 32 + 32 * s for t in {0, ntiles - 1} for qs in range(split)
+                  for s in range(nsub)}
+        for key0 in {0, (N - 1) // bk * bk, max(0, (N // bk - 1) * bk)}:
+            rows = min(bk, N - key0)
+            for i in starts:
+                if rows == bk:
+                    soff = last32 if tile > bk and i > last32 else i
+                    assert key0 * N + (bk - 1) * N + 16 + soff + 16 <= N * N
+                    assert soff == i or i >= N         # the queries that exist are read in place
+                else:
+                    for row in {0, rows - 1}:
+                        for g in (0, 1):
+                            v = row * N + 16 * g + i
+                            assert all(key0 * N + x + 4 <= N * N for x in range(v, v + 16, 4) if x + 4 <= rows * N)
