@@ -234,11 +234,9 @@ __global__ __launch_bounds__(kThreads, DS <= 16 ? 4 : 2) void fwd_short_bf16_ker
   // the copy keeps four waves per SIMD without spilling
   constexpr bool ALT = DS >= 32 || XP;
   // Padding rows (zero): the K rows of block nkb mod 8, read past the last
-  // block of a sequence (the product is never used), and at N <= 32 the K
-  // and V rows of the masked second block of the last slice stay in the
-  // arrays (their P is 0, and the V rows must be finite)
-  constexpr int KROWS = ROWS + 64, VROWS = ROWS + 32;
-  __shared__ __attribute__((aligned(16))) uint16_t sK[KROWS * D], sV[VROWS * D];
+  // block of a sequence (the product is never used)
+  constexpr int KROWS = ROWS + 64;
+  __shared__ __attribute__((aligned(16))) uint16_t sK[KROWS * D], sV[ROWS * D];
   __shared__ __attribute__((aligned(16))) float sTab[kShortTabEntries * 64];
 
   const int tid = threadIdx.x;
@@ -246,9 +244,12 @@ __global__ __launch_bounds__(kThreads, DS <= 16 ? 4 : 2) void fwd_short_bf16_ker
   const int col = lane & 31, g = lane >> 5;
   const uint32_t lane4 = (uint32_t)lane * 4u;
   const int N = (int)a.Sq;
-  // key blocks: at least 2 (N <= 32 has a second block whose keys are all
-  // masked, so the spd stream below needs no case of its own)
+  // key blocks: at least 2 in the spd stream, which then needs no case of its
+  // own; at N <= 32 the second has no key and is not computed (its K and V rows
+  // are the next sequence's: a mask of -inf and P = 0 would not hold off their
+  // infinities and NaN)
   const int nkb = N > 32 ? (N + 31) / 32 : 2;
+  const bool one = TAIL && N <= 32;
   // P sequences of the head at once (N <= 128: 2, N <= 64: 4, N <= 32: 8):
   // sequence slot p = w / GW of a group holds LDS rows p R .. p R + R - 1
   // and its waves take query blocks wl = w mod GW.
@@ -289,7 +290,7 @@ __global__ __launch_bounds__(kThreads, DS <= 16 ? 4 : 2) void fwd_short_bf16_ker
       const int lo = row * D + swz_tile<D>(row, ch) * 8;
       const bool k1 = XP && ch == 3, v1 = XP && ch == 1;
       *reinterpret_cast<uint4*>(sK + lo) = make_uint4(k1 ? kOne | (kOne << 16) : 0u, k1 ? kOne : 0u, 0u, 0u);
-      if (row < VROWS) *reinterpret_cast<uint4*>(sV + lo) = make_uint4(v1 ? kOne : 0u, 0u, 0u, 0u);
+      if (row < ROWS) *reinterpret_cast<uint4*>(sV + lo) = make_uint4(v1 ? kOne : 0u, 0u, 0u, 0u);
     }
   }
 
@@ -454,8 +455,8 @@ __global__ __launch_bounds__(kThreads, DS <= 16 ? 4 : 2) void fwd_short_bf16_ker
         spd_load(src, here ? rem_s : rem_n, (uint32_t)((here ? kf : kf - nkb) * 32), wd[(kb + 2) % 3]);
       }
       sched_fence();
-      if (wact) {
-        {
+      if (wact && !(kb == 1 && one)) {
+        if (!(kb == 0 && one)) {
           uint32_t e[4];
           entries(wd[(kb + 1) % 3], kb + 1, e);
           issue_scores<D, NKP>(sTab, e, lane4, sKp, off.k, (kb + 1) & 7, qf, sn);
@@ -473,7 +474,9 @@ __global__ __launch_bounds__(kThreads, DS <= 16 ? 4 : 2) void fwd_short_bf16_ker
           else
             softmax_pv<D, false>(sc, vop, 32, sl2, st, acc);
         }
-        if constexpr (!ALT) sc = sn;
+        if constexpr (!ALT) {
+          if (!(kb == 0 && one)) sc = sn;
+        }
       }
     };
     if constexpr (ALT) {
