@@ -179,9 +179,11 @@ __device__ __forceinline__ void product_rows(const float* t, const float (&f)[D 
 // the rows; lanes of rows past a narrow head dim repeat its features (their
 // results are not used). The block's 32 terms are summed on their own and
 // then added: one accumulator over all rows would gather their rounding (N =
-// 3327, d = 64: O off by 9.7e-7 of 64 bits instead of 5.2e-7).
+// 3327, d = 64: O off by 9.7e-7 of 64 bits instead of 5.2e-7). A column with
+// keep false takes nothing from the block, whatever its rows hold.
 template <int D>
-__device__ __forceinline__ void product_cols(const float* t, const float (&b)[16], f32x16 (&acc)[kBlocksF<D>]) {
+__device__ __forceinline__ void product_cols(const float* t, const float (&b)[16], f32x16 (&acc)[kBlocksF<D>],
+                                             bool keep = true) {
   const int lane = threadIdx.x & 63;
   const float* p = t + 16 * (lane >> 5) * kRowF<D> + (D == 64 ? 2 * (lane & 31) : (lane & (D - 1) & 31));
   f32x16 x[kBlocksF<D>];
@@ -196,6 +198,12 @@ __device__ __forceinline__ void product_cols(const float* t, const float (&b)[16
     } else {
       x[0] = mfma32f(p[r * kRowF<D>], b[r], x[0]);
     }
+  }
+  if (!__all(keep)) {
+#pragma unroll
+    for (int c = 0; c < kBlocksF<D>; ++c)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) x[c][r] = keep ? x[c][r] : 0.0f;
   }
 #pragma unroll
   for (int c = 0; c < kBlocksF<D>; ++c)

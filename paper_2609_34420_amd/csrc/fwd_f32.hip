@@ -113,7 +113,11 @@ __global__ __launch_bounds__(kThreadsF, 1) void fwd_f32_kernel(FwdArgs a) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) bs += p[r];
       l += bs;
-      product_cols<D>(sV + r0 * kRowF<D>, p, acc);
+      // a row without a score in the block (every p 0, none NaN) takes nothing
+      // from it: 0 times a non-finite value would be NaN
+      bool keep = true;
+      if (__any(mx == -INFINITY)) keep = mx != -INFINITY || bs + __shfl_xor(bs, 32) != 0.0f;
+      product_cols<D>(sV + r0 * kRowF<D>, p, acc, keep);
     }
   }
 
