@@ -10,9 +10,12 @@
 // the others', N = 1500, d = 64: in the buckets that row does not hold dtable is
 // off by 8e-7 of 64 bits, 8e-4 with the terms rounded down; dO 1e6 times 4e-6
 // and 7e-3.) And a row's terms sum to at most the bound in magnitude (the P of a row sum
-// to at most 1), so a workgroup's 256 rows stay below 2^62. A term outside that
-// range (infinite or NaN inputs, an LSE that is not the inputs') is added to
-// dtable itself as a float, so it shows there.
+// to at most 1). Neither is taken for granted: a term whose dO_i.V_j - Dlt_i is
+// not below 2^(53 - F) (infinite or NaN inputs, rows whose squared norm
+// overflows: the bound leaves their block of 256 out) and, once the P of a lane's half row
+// sum to more than 1.5, all its further terms (an LSE that is not the inputs')
+// are added to dtable itself as floats. So each of a workgroup's 512 lanes adds
+// less than 1.5 2^53 and the sums stay below 2^63.
 #include "f32_mfma.hpp"
 
 namespace gt {
@@ -30,14 +33,16 @@ __device__ __forceinline__ unsigned long long fixed64(float xs) {
   return ((unsigned long long)(uint32_t)((int)hi + (l >> 31)) << 32) | (uint32_t)l;
 }
 
-// The block maxima (a.nmax) of head h0 and of the same head of the next ns - 1
-// sequences, reduced over the workgroup, as the fixed-point exponent F.
+// The maxima (a.nmax) of the blocks of head h0 and of the same head of the next
+// ns - 1 sequences that are finite, reduced over the workgroup, as the
+// fixed-point exponent F.
 __device__ __forceinline__ int fixed_exponent(const BwdArgs& a, int h0, int ns, float (*red)[kWavesF]) {
   const int tid = threadIdx.x;
   const int64_t nblk = ((a.Sq > a.Sk ? a.Sq : a.Sk) + 255) / 256;
   float v[3] = {0.0f, 0.0f, 0.0f};
   for (int64_t t = tid; t < ns * nblk; t += kThreadsF) {
     const float* nm = a.nmax + ((h0 + t / nblk * a.hpb) * nblk + t % nblk) * 4;
+    if (!(fmaxf(fmaxf(nm[0], nm[1]), nm[2]) < INFINITY)) continue;
 #pragma unroll
     for (int c = 0; c < 3; ++c) v[c] = fmaxf(v[c], nm[c]);
   }
@@ -137,6 +142,8 @@ __global__ __launch_bounds__(kThreadsF, 1) void bwd_dq_f32_kernel(BwdArgs a) {
   f32x16 acc[NA];
 #pragma unroll
   for (int c = 0; c < NA; ++c) acc[c] = zero_f32x16();
+  const float lim = 0x1p53f / sF;
+  float psum = 0.0f;                             // of this lane half's P
   for (int64_t t = 0; t < ntiles; ++t) {
     lds_barrier();
     tile.store(sK, sV);
@@ -158,24 +165,34 @@ __global__ __launch_bounds__(kThreadsF, 1) void bwd_dq_f32_kernel(BwdArgs a) {
       f32x16 s = zero_f32x16(), dp = zero_f32x16();
       product_rows<D>(sK + r0 * kRowF<D>, qf, s);
       product_rows<D>(sV + r0 * kRowF<D>, df, dp);
-      float ds[16];
+      float ds[16];                              // P, then dS
 #pragma unroll
-      for (int r = 0; r < 16; ++r) ds[r] = exp2_fast((s[r] + tb[r] - L) * kLog2e) * (dp[r] - dlt);
-      if (jrem < 32) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) ds[r] = 16 * g + r < jrem ? ds[r] : 0.0f;
+      for (int r = 0; r < 16; ++r) {
+        ds[r] = exp2_fast((s[r] + tb[r] - L) * kLog2e);
+        dp[r] -= dlt;
       }
-      float xs[16];
+      if (jrem < 32) {                           // keys past the last
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          ds[r] = 16 * g + r < jrem ? ds[r] : 0.0f;
+          dp[r] = 16 * g + r < jrem ? dp[r] : 0.0f;
+        }
+      }
       bool wild = false;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        xs[r] = ds[r] * sF;
-        wild |= !(fabsf(xs[r]) < 0x1p60f);
+        psum += ds[r];
+        wild |= !(fabsf(dp[r]) < lim);
+        ds[r] *= dp[r];
       }
-      if (__any(wild)) {
+      const bool row_wild = !(psum <= 1.5f);
+      float xs[16];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) xs[r] = ds[r] * sF;
+      if (__any(wild || row_wild)) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          if (fabsf(xs[r]) < 0x1p60f) continue;
+          if (!row_wild && fabsf(dp[r]) < lim) continue;
           const int b = (int)(off[r] >> SHIFT);
           if (b < a.n_buckets) atomicAdd(&dtable_h[b], ds[r]);
           xs[r] = 0.0f;

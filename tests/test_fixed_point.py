@@ -43,3 +43,11 @@ def test_fixed64_rounds_to_nearest(fixed64, sign):
             continue
         got = fixed64(x)
         assert abs(got - int(x) - (x - int(x))) <= 0.5, (x, got)
+
+
+def test_f32_histogram_range():
+    """A lane adds terms below 2^53 times its P, and none once those sum to
+    more than 1.5; 512 lanes at most share a sum."""
+    text = SRC.read_text()
+    lim, psum = re.search(r"lim = 0x1p(\d+)f / sF", text), re.search(r"row_wild = !\(psum <= ([\d.]+)f\)", text)
+    assert float(psum.group(1)) * 2 ** int(lim.group(1)) * 512 < 2 ** 63
