@@ -66,7 +66,8 @@ constexpr int kQB = 2;             // 32-query blocks per wave
 // (8 and 16 run on 32-wide tiles whose extra features are zero).
 template <int D, int DS, bool OUT_F32, int KS, SpdRows ROWS>
 __global__ __launch_bounds__(kThreads, 1) void fwd_bf16_kernel(FwdArgs a) {
-  constexpr bool RAG = ROWS != kWhole;
+  constexpr bool RAG = ROWS != kWhole;        // ragged rows, and
+  constexpr bool RAGK = !whole_keys(ROWS);    // ragged keys
   constexpr int NKC = D / 16;
   constexpr int NKS = (DS + 15) / 16;   // feature chunks that hold data
   constexpr int NCB = D / 32;
@@ -75,7 +76,7 @@ __global__ __launch_bounds__(kThreads, 1) void fwd_bf16_kernel(FwdArgs a) {
   constexpr int TR = split_tile_rows<D, KS>();
   constexpr int KB = TR / (32 * KS);    // 32-key blocks per wave and tile
   static_assert(KB == 1 || KB == 2, "one or two key blocks per wave and tile");
-  static_assert(RAG || KS == 1, "the key-split kernels take every size");
+  static_assert(RAGK || KS == 1, "the key-split kernels take every size");
   using Dma = TileDma<D, kWaves, DS, TR>;   // K and V
 
   // Three-stage ring of K / V tiles, one array per stage so that no read of
@@ -185,7 +186,7 @@ __global__ __launch_bounds__(kThreads, 1) void fwd_bf16_kernel(FwdArgs a) {
     if constexpr (NS == 1) spd.fetch(tt + 1, srow[qb], kb, wu);
   };
   using Main = std::false_type;
-  using End = std::integral_constant<bool, RAG>;
+  using End = std::integral_constant<bool, RAGK>;
   using P0 = std::integral_constant<int, 0>;
   using P1 = std::integral_constant<int, 1>;
   f32x16 s0;        // score accumulator of the current tile's first unit
@@ -267,7 +268,7 @@ __global__ __launch_bounds__(kThreads, 1) void fwd_bf16_kernel(FwdArgs a) {
       softmax_pv<D, END>(s1, vop, jrem, sl2, sm[1], acc[1]);
   };
   {
-    const int64_t nmain = RAG ? ntiles - 1 : ntiles;
+    const int64_t nmain = RAGK ? ntiles - 1 : ntiles;
     int64_t t = 0;
     for (; t + 6 <= nmain; t += 6) {
       step(t, S0(), P0(), Main());
@@ -282,7 +283,7 @@ __global__ __launch_bounds__(kThreads, 1) void fwd_bf16_kernel(FwdArgs a) {
     if (t + 2 < ntiles) step(t + 2, S2(), P0(), End());
     if (t + 3 < ntiles) step(t + 3, S0(), P1(), End());
     if (t + 4 < ntiles) step(t + 4, S1(), P0(), End());
-    if constexpr (RAG) {
+    if constexpr (RAGK) {
       if (t + 5 < ntiles) step(t + 5, S2(), P1(), End());
     }
   }
@@ -399,8 +400,11 @@ void launch_fwd_ks(const FwdArgs& a, hipStream_t s) {
     return;
   }
   if constexpr (KS == 1) {
-    if (a.Sq % BR == 0 && a.Sk % split_tile_rows<D, KS>() == 0) {
-      hipLaunchKernelGGL((fwd_bf16_kernel<D, DS, OUT_F32, KS, kWhole>), grid, dim3(kThreads), 0, s, a);
+    if (a.Sk % split_tile_rows<D, KS>() == 0) {
+      if (a.Sq % BR == 0)
+        hipLaunchKernelGGL((fwd_bf16_kernel<D, DS, OUT_F32, KS, kWhole>), grid, dim3(kThreads), 0, s, a);
+      else
+        hipLaunchKernelGGL((fwd_bf16_kernel<D, DS, OUT_F32, KS, kWholeKeys>), grid, dim3(kThreads), 0, s, a);
       return;
     }
   }

@@ -190,7 +190,7 @@ def test_loads_that_may_pass_the_end_have_no_scalar_offset():
             callers.append((f.name, m.group(1)))
         assert text.count("buf_u128_inside(") == (f.name == "common.hpp") + sum(c[0] == f.name for c in callers)
     assert callers == [("bwd_dkdv.hip", "if constexpr (!KTAIL)"), ("fwd_short.hip", "else"),
-                       ("stage.hpp", "if constexpr (ROWS == kWhole)")]
+                       ("stage.hpp", "if constexpr (whole_keys(ROWS))")]
     text = (CSRC / "fwd_short.hip").read_text()
     assert re.search(r"else if constexpr \(TAIL\)\n\s*buf_u128\(.*\n\s*else\n\s*buf_u128_inside", text)
 
