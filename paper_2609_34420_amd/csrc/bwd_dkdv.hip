@@ -653,9 +653,7 @@ void launch_dkdv_qs(const BwdArgs& a, hipStream_t s) {
 
 template <int D, int DS, int NB>
 void launch_dkdv_t(const BwdArgs& a, hipStream_t s) {
-  const int qs = pick_split(a.Sk, a.Sq, a.H, kNW * 32, dkdv_tile_rows<D, 1>(), dkdv_tile_rows<D, 2>(),
-                            dkdv_tile_rows<D, 4>());
-  switch (qs) {
+  switch (pick_split(a.Sk, a.Sq, a.H, dkdv_split_cost(D))) {
     case 1: launch_dkdv_qs<D, DS, NB, 1>(a, s); break;
     case 2: launch_dkdv_qs<D, DS, NB, 2>(a, s); break;
     default: launch_dkdv_qs<D, DS, NB, 4>(a, s); break;

@@ -433,7 +433,7 @@ void launch_dq_ks(const BwdArgs& a, hipStream_t s) {
 
 template <int D, int DS>
 void launch_dq_t(const BwdArgs& a, hipStream_t s) {
-  switch (pick_split(a.Sq, a.Sk, a.H, kWaves * 32, split_tile_rows<D, 1>(), split_tile_rows<D, 2>(), split_tile_rows<D, 4>())) {
+  switch (pick_split(a.Sq, a.Sk, a.H, dq_split_cost(D))) {
     case 1: launch_dq_ks<D, DS, 1>(a, s); break;
     case 2: launch_dq_ks<D, DS, 2>(a, s); break;
     default: launch_dq_ks<D, DS, 4>(a, s); break;

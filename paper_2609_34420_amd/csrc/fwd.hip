@@ -10,18 +10,20 @@ namespace gt {
 // side's columns. A split costs copies, barriers and the combination of the
 // groups, so it pays only where the unsplit grid leaves compute units idle:
 // the smallest of rounds over the 256 compute units times the time of one
-// workgroup, in units of one tile step of 2 blocks per wave (1.2-1.3 us in the
-// d = 64 forward; a step of one block measured 0.55 of it, setting a workgroup
-// up and finishing it about three steps).
-int pick_split(int64_t rows, int64_t cols, int64_t heads, int rows1, int tile1, int tile2, int tile4) {
+// workgroup (SplitCost). The constants are fits to each kernel with 1, 2 and 4
+// groups over 108 grids per head dim (4 to 32768 heads, 64 to 24000 rows): the
+// choice is 0.1-0.3 % off the best of the three on average, 10 % at worst. With
+// one step time and one setup for all it was 34 % off where many short
+// sequences fill the chip as it is (forward, d = 64, 32768 heads of 64 rows: 1063 /
+// 1501 / 1422 us with 1 / 2 / 4; 16384 of 128: 694 / 787 / 826).
+int pick_split(int64_t rows, int64_t cols, int64_t heads, const SplitCost& c) {
   int best = 1;
   double best_cost = 0.0;
-  for (int ks = 1; ks <= 4; ks *= 2) {
-    const int64_t wgs = (rows + rows1 / ks - 1) / (rows1 / ks) * heads;
-    const int64_t rounds = (wgs + 255) / 256;
-    const int tile = ks == 1 ? tile1 : (ks == 2 ? tile2 : tile4);
-    const double step = tile / (32 * ks) == 2 ? 1.0 : 0.55;
-    const double cost = (double)rounds * ((double)((cols + tile - 1) / tile) * step + 3.0);
+  for (int ks = 1, l = 0; ks <= 4; ks *= 2, ++l) {
+    const int64_t br = c.rows1 / ks;
+    const int64_t rounds = ((rows + br - 1) / br * heads + 255) / 256;
+    const double step = c.step[l] * (2 * rows <= br ? c.half : 1.0);
+    const double cost = (double)rounds * ((double)((cols + c.tile[l] - 1) / c.tile[l]) * step + c.setup[l]);
     if (ks == 1 || cost < best_cost) {
       best = ks;
       best_cost = cost;
@@ -55,7 +57,7 @@ int pick_split_f32(int64_t rows, int64_t cols, int64_t heads, int D) {
 }
 
 int fwd_key_split(const FwdArgs& a, int D) {
-  return pick_split(a.Sq, a.Sk, a.H, 512, 64, 128, D == 64 ? 128 : 256);
+  return pick_split(a.Sq, a.Sk, a.H, fwd_split_cost(D));
 }
 
 hipError_t launch_fwd(const FwdArgs& a, int d, bool bf16, bool out_f32, hipStream_t s) {

@@ -97,9 +97,30 @@ hipError_t launch_fwd(const FwdArgs& a, int d, bool bf16, bool out_f32, hipStrea
 template <int D, int DS, bool OUT_F32>
 hipError_t launch_fwd_mfma(const FwdArgs& a, hipStream_t s);
 int fwd_key_split(const FwdArgs& a, int D);
+// What a split into 1, 2 and 4 groups costs (index 0, 1, 2): the columns of a
+// tile, the time of a tile and of a workgroup's setup, end and combination, in
+// tiles of the unsplit kernel. half: the share of a tile's time where at most
+// half of a workgroup's waves have rows.
+struct SplitCost {
+  int rows1;
+  int tile[3];
+  double step[3], setup[3], half;
+};
+// Forward and dQ: a tile holds 2 blocks of 32 keys per wave, 1 with 4 groups at
+// d = 64. dK/dV: 2 blocks of 32 queries, 1 with 4 groups and, at d = 64, with 2.
+inline SplitCost fwd_split_cost(int D) {
+  return {512, {64, 128, D == 64 ? 128 : 256}, {1.0, 1.04, D == 64 ? 0.58 : 1.04}, {3.5, 4.2, 4.4}, 0.6};
+}
+inline SplitCost dq_split_cost(int D) {
+  return {256, {64, 128, D == 64 ? 128 : 256}, {1.0, 1.06, D == 64 ? 0.6 : 1.06}, {4.0, 4.6, 4.6}, 0.55};
+}
+inline SplitCost dkdv_split_cost(int D) {
+  if (D == 64) return {256, {64, 64, 128}, {1.0, 0.54, 0.61}, {3.0, 3.0, 3.0}, 1.0};
+  return {256, {64, 128, 128}, {1.0, 0.98, 0.55}, {2.5, 2.5, 2.5}, 1.0};
+}
 // The split ks = 1, 2 or 4 that finishes first, for workgroups of rows1 / ks
-// rows over tiles of tile1, tile2, tile4 columns.
-int pick_split(int64_t rows, int64_t cols, int64_t heads, int rows1, int tile1, int tile2, int tile4);
+// rows.
+int pick_split(int64_t rows, int64_t cols, int64_t heads, const SplitCost& c);
 // Sequences of at most 256 rows (bf16 in and out, at most 127 buckets): the
 // persistent whole-sequence forward.
 bool fwd_short_applies(const FwdArgs& a, int d);
