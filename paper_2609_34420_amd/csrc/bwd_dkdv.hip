@@ -103,7 +103,10 @@ struct DkdvTable {
   static constexpr int ENT = NB * CPY;            // entry (b, c) = b * CPY + c
   uint2 tabw[ENT];                  // table copies (fp32 bits, 8-byte stride)
   unsigned long long hist[ENT];     // gradient histogram copies, same index
-  __device__ __forceinline__ void set_table(int t, float v) { tabw[t] = make_uint2(__float_as_uint(v), 0u); }
+  static constexpr int PER16 = 2;                 // entries in 16 bytes
+  __device__ __forceinline__ void set16(int t, float v) {
+    reinterpret_cast<uint4*>(tabw)[t] = make_uint4(__float_as_uint(v), 0u, __float_as_uint(v), 0u);
+  }
 };
 template <int NB>
 struct DkdvTable<NB, kHalved> {
@@ -111,7 +114,10 @@ struct DkdvTable<NB, kHalved> {
   static constexpr int ENT = NB * CPY;
   float tab[ENT];
   unsigned long long hist[ENT];
-  __device__ __forceinline__ void set_table(int t, float v) { tab[t] = v; }
+  static constexpr int PER16 = 4;
+  __device__ __forceinline__ void set16(int t, float v) {
+    reinterpret_cast<float4*>(tab)[t] = make_float4(v, v, v, v);
+  }
 };
 template <int D, int NB, int BQ, DkdvForm F = dkdv_form<D, NB, BQ>()>
 struct DkdvSmem : DkdvTiles<D, BQ>, DkdvRows<BQ> {
@@ -577,12 +583,15 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dkdv_bf16_kernel(BwdArgs a) {
   const int64_t j = kblk * kBK + (QS == 1 ? wave : wave % (kNW / QS)) * 32 + col;
   const bool jok = j < a.Sk;
 
-  for (int t = tid; t < Table::ENT; t += kThreads) {
-    const int bkt = t / CPY;
-    const float tv = (bkt < a.n_buckets) ? a.table[(int64_t)table_row(a, h) * a.n_buckets + bkt] * kLog2e : 0.0f;
-    sm.t.set_table(t, tv);
-    hist[t] = 0ull;
+  // 16 bytes per store; the histogram of the table's buckets only (what other
+  // byte values add is not read). Sequences of 64 rows, 200 buckets, d = 64, 32768
+  // heads: 1415 us with an entry per store and the whole histogram cleared, 1193 so.
+  for (int t = tid; t < Table::ENT / Table::PER16; t += kThreads) {
+    const int bkt = t * Table::PER16 / CPY;
+    sm.t.set16(t, bkt < a.n_buckets ? a.table[(int64_t)table_row(a, h) * a.n_buckets + bkt] * kLog2e : 0.0f);
   }
+  for (int t = tid; t < a.n_buckets * CPY / 2; t += kThreads)
+    reinterpret_cast<uint4*>(hist)[t] = make_uint4(0u, 0u, 0u, 0u);
 
   // Fixed-point exponent F of this head: (max|dO| max|V| + max|Dlt|) 2^F
   // <= 2^30 (a 1.5 % margin covers the rounding of P and of the products).

@@ -108,6 +108,28 @@ def test_many_buckets_bf16(H, Sq, Sk, d, first, pad, nb):
     run_case("bf16", H, Sq, Sk, d, first, pad, nb)
 
 
+# The histogram is cleared for the table's buckets only: every layout with one,
+# two and three buckets, and with bytes far past them.
+@pytest.mark.parametrize("H,Sq,Sk,d,nb", [(1, 70, 100, 64, 1), (1, 70, 100, 8, 3), (256, 300, 300, 64, 2),
+                                          (128, 300, 300, 64, 1), (1, 130, 300, 64, 128), (256, 300, 300, 64, 129)])
+def test_few_buckets_of_many_bytes_bf16(H, Sq, Sk, d, nb):
+    g = np.random.default_rng(nb)
+    spd = g.integers(0, 256, size=(Sq, Sk)).astype(np.uint8)
+    q, k, v, do = (synth.round_bf16(g.standard_normal((H, n, d)).astype(np.float32)) for n in (Sq, Sk, Sk, Sq))
+    table = (g.standard_normal((H, nb)) * 0.5).astype(np.float32)
+    scale = 1.0 / np.sqrt(d)
+    say(f"few buckets H={H} Sq={Sq} Sk={Sk} d={d} nb={nb}")
+    bf = torch.bfloat16
+    o, l = oracle.ring_step(q, k, v, spd, 0, 0, table, scale)
+    o, l = synth.round_bf16(o.astype(np.float32)), l.astype(np.float32)
+    acc = gt.gt_attn_bwd_ring_step(to_dev(q, bf), to_dev(o, bf), to_dev(l), to_dev(do, bf), to_dev(k, bf), to_dev(v, bf),
+                                   to_dev(spd, torch.uint8), 0, 0, to_dev(table), scale=scale)
+    torch.cuda.synchronize()
+    ref = oracle.ring_backward_step(q, o, l, do, k, v, spd, 0, 0, table, scale)
+    names = ("dq", "dk", "dv", "dtable")
+    check_grads(f"few buckets nb={nb}", dict(zip(names, (to_np(x) for x in acc))), dict(zip(names, ref)), "bf16")
+
+
 @pytest.mark.parametrize("H,Sq,Sk,d,first,pad,nb", CASES)
 def test_any_size_f32(H, Sq, Sk, d, first, pad, nb):
     run_case("f32", H, Sq, Sk, d, first, pad, nb)
