@@ -109,10 +109,12 @@ struct SplitCost {
 // Forward and dQ: a tile holds 2 blocks of 32 keys per wave, 1 with 4 groups at
 // d = 64. dK/dV: 2 blocks of 32 queries, 1 with 4 groups and, at d = 64, with 2.
 inline SplitCost fwd_split_cost(int D) {
-  return {512, {64, 128, D == 64 ? 128 : 256}, {1.0, 1.04, D == 64 ? 0.58 : 1.04}, {3.5, 4.2, 4.4}, 0.6};
+  if (D == 64) return {512, {64, 128, 128}, {1.0, 1.06, 0.61}, {3.5, 4.4, 4.4}, 0.6};
+  return {512, {64, 128, 256}, {1.0, 1.04, 1.04}, {3.5, 4.4, 4.4}, 0.6};
 }
 inline SplitCost dq_split_cost(int D) {
-  return {256, {64, 128, D == 64 ? 128 : 256}, {1.0, 1.06, D == 64 ? 0.6 : 1.06}, {4.0, 4.6, 4.6}, 0.55};
+  if (D == 64) return {256, {64, 128, 128}, {1.0, 1.07, 0.62}, {4.0, 4.6, 4.6}, 0.55};
+  return {256, {64, 128, 256}, {1.0, 1.06, 1.06}, {4.0, 4.6, 4.6}, 0.55};
 }
 inline SplitCost dkdv_split_cost(int D) {
   if (D == 64) return {256, {64, 64, 128}, {1.0, 0.54, 0.61}, {3.0, 3.0, 3.0}, 1.0};

@@ -302,7 +302,8 @@ struct SpdStream {
   // there to the last query row's last key.
   __device__ __forceinline__ SpdStream(const uint8_t* row0, int64_t bytes, int64_t Sk, int part_, int g)
       : rem(BYTES ? (uint32_t)(reinterpret_cast<uintptr_t>(row0) & 15u) : 0u), base(row0 - rem),
-        range(rsrc_range((bytes + rem + 3) & ~(int64_t)3)), rs(make_rsrc(row0)), ntiles((Sk + TR - 1) / TR), part(part_), g16(16 * g) {}
+        range(rsrc_range((bytes + rem + 3) & ~(int64_t)3)), rs(make_rsrc(row0)), ntiles((Sk + TR - 1) / TR),
+        part(part_), g16(16 * g) {}
   __device__ __forceinline__ Row row(int64_t bytes) const {    // bytes: from the wave's first row
     Row r;
     r.voff = (uint32_t)bytes + (uint32_t)g16 + rem;

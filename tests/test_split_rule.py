@@ -18,6 +18,8 @@ MEASURED = [
     ("fwd", 8192, 256, 64, 520, 572, 928), ("fwd", 1600, 576, 64, 432, 441, 543),
     ("fwd", 192, 1536, 64, 197, 212, 232), ("fwd", 8, 8256, 64, 277, 313, 275),
     ("fwd", 16, 4096, 64, 142, 89, 104), ("fwd", 8, 4160, 64, 145, 82, 102),
+    ("fwd", 16, 6000, 64, 216, 239, 227), ("fwd", 16, 5500, 64, 198, 223, 199),
+    ("dq", 4, 8256, 64, 190, 215, 198), ("dq", 4, 9000, 64, 209, 239, 216),
     ("fwd", 8, 16384, 64, 655, 662, 737), ("fwd", 16384, 128, 8, 485, 516, 676),
     ("fwd", 8, 8256, 8, 234, 243, 197), ("fwd", 16, 4096, 8, 115, 65, 73),
     ("dq", 32768, 64, 64, 991, 1218, 1243), ("dq", 16384, 128, 64, 654, 710, 1218),
@@ -64,4 +66,6 @@ def test_cost_constants_match_the_kernels(pick):
     text = (CSRC / "stage.hpp").read_text() + (CSRC / "bwd_dkdv.hip").read_text()
     assert "64 * KS < (D == 64 ? 128 : 256) ? 64 * KS : (D == 64 ? 128 : 256)" in text
     assert "D == 64 && QS == 2 ? 64 : (QS == 1 ? 64 : 128)" in text
-    assert "{512, {64, 128, D == 64 ? 128 : 256}" in (CSRC / "kernels.hpp").read_text()
+    head = (CSRC / "kernels.hpp").read_text()
+    for rows in (512, 256):
+        assert f"{{{rows}, {{64, 128, 128}}" in head and f"{{{rows}, {{64, 128, 256}}" in head
