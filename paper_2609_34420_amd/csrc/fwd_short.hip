@@ -214,9 +214,14 @@ __device__ __forceinline__ void softmax_first(const f32x16& s, const bf16x8 (&vo
 // forward that took these before (its 64 KB table filled per workgroup and one
 // workgroup per compute unit): 512 x 203 nodes, d = 32 206 -> 106 us, 8192 x 30, d = 8
 // 3790 -> 88; d = 64: 512 x 256 247 -> 177, 4000 x 33 2242 -> 148.
+// WIDE: 128 to 256 buckets. The table then has an entry for every byte value
+// (64 KB, one workgroup per compute unit at every head dim), and the scores of
+// keys past N start from -inf by a select in the sequence's last block. 1024 x
+// 256 nodes, H = 8, 256 buckets: d = 8 309 us on the full-width kernel, 150 here, d =
+// 64 533 and 350; 4096 x 64, 200 buckets, d = 8: 589 and 74.
 constexpr int kShortTabEntries = 129;
-template <int DS, bool TAIL, bool ANY>
-__global__ __launch_bounds__(kThreads, DS <= 16 ? 4 : 2) void fwd_short_bf16_kernel(FwdArgs a) {
+template <int DS, bool TAIL, bool ANY, bool WIDE>
+__global__ __launch_bounds__(kThreads, DS <= 16 && !WIDE ? 4 : 2) void fwd_short_bf16_kernel(FwdArgs a) {
   constexpr int D = DS == 64 ? 64 : 32;
   constexpr int CPR = D / 8;                    // 16-byte chunks per LDS row
   constexpr int NWD = ANY ? 5 : 4;              // dwords of a spd group in flight
@@ -237,7 +242,8 @@ __global__ __launch_bounds__(kThreads, DS <= 16 ? 4 : 2) void fwd_short_bf16_ker
   // block of a sequence (the product is never used)
   constexpr int KROWS = ROWS + 64;
   __shared__ __attribute__((aligned(16))) uint16_t sK[KROWS * D], sV[ROWS * D];
-  __shared__ __attribute__((aligned(16))) float sTab[kShortTabEntries * 64];
+  constexpr int ENTRIES = WIDE ? 256 : kShortTabEntries;
+  __shared__ __attribute__((aligned(16))) float sTab[ENTRIES * 64];
 
   const int tid = threadIdx.x;
   const int lane = tid & 63, w = wave_id();
@@ -273,15 +279,16 @@ __global__ __launch_bounds__(kThreads, DS <= 16 ? 4 : 2) void fwd_short_bf16_ker
   const FwdOffsets<D> off;
 
   // table entry (b, lane) at float 64 b + lane: bias / scale (XP: bias
-  // log2 e) for b below n_buckets, 0 up to 127, -inf at 128; zero K, V
+  // log2 e) for b below n_buckets, 0 up to 127, -inf at 128 (WIDE: 0 up to 255);
+  // zero K, V
   // (features past the head dim stay zero; XP: the ones of feature 24..26
   // of K and feature 8 of V)
   {
     const float tmul = XP ? kLog2e : 1.0f / a.scale;
     const float* th = a.table + (int64_t)head * a.n_buckets;
-    for (int t = tid; t < kShortTabEntries * 16; t += kThreads) {
+    for (int t = tid; t < ENTRIES * 16; t += kThreads) {
       const int bk = t >> 4;
-      const float x = bk < 128 ? (bk < a.n_buckets ? th[bk] * tmul : 0.0f) : -INFINITY;
+      const float x = WIDE || bk < 128 ? (bk < a.n_buckets ? th[bk] * tmul : 0.0f) : -INFINITY;
       reinterpret_cast<float4*>(sTab)[t] = make_float4(x, x, x, x);
     }
     constexpr uint32_t kOne = 0x3f80u;           // bf16 1.0
@@ -351,7 +358,8 @@ __global__ __launch_bounds__(kThreads, DS <= 16 ? 4 : 2) void fwd_short_bf16_ker
       buf_u128_inside(r, voff, j, w);
   };
   // Bucket words of key block kb as table entries: bytes of 128 or more to
-  // the padding entry 127; with TAIL, keys past N to the -inf entry.
+  // the padding entry 127; with TAIL, keys past N to the -inf entry. (WIDE: the
+  // bytes as they are.)
   uint32_t sh = 0;                              // ANY: this sequence's row address mod 4
   auto entries = [&](const uint32_t (&wsrc)[NWD], int kb, uint32_t (&e)[4]) {
     uint32_t x[NWD];
@@ -363,6 +371,7 @@ __global__ __launch_bounds__(kThreads, DS <= 16 ? 4 : 2) void fwd_short_bf16_ker
     if constexpr (ANY) align_spd5(x, sh);
 #pragma unroll
     for (int u = 0; u < 4; ++u) e[u] = x[u];
+    if constexpr (WIDE) return;
     if (__any(((e[0] | e[1] | e[2] | e[3]) & 0x80808080u) != 0)) {
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
@@ -441,6 +450,21 @@ __global__ __launch_bounds__(kThreads, DS <= 16 ? 4 : 2) void fwd_short_bf16_ker
     st.l = 0.0f;
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb) acc[cb] = zero_f32x16();
+    // Scores of key block kb with the bias entries e.
+    auto scores = [&](const uint32_t (&e)[4], int kb, f32x16& s) {
+      if constexpr (WIDE && TAIL) {
+        load_bias(sTab, e, lane4, s);
+        if (kb * 32 + 32 > N) {
+          uint32_t left = (uint32_t)(N - kb * 32 - 16 * g);   // keys of this lane half
+          opaque(left);                          // (its 16 comparisons are not kept for every block)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) s[r] = r < (int)left ? s[r] : -INFINITY;
+        }
+        add_scores<D, NKP>(sKp, off.k, kb & 7, qf, s);
+      } else {
+        issue_scores<D, NKP>(sTab, e, lane4, sKp, off.k, kb & 7, qf, s);
+      }
+    };
     // Key block kb: the words of block kb + 2 are fetched (of the next
     // sequence past the end: one load whatever the source, so the wait for
     // block kb + 1's words leaves it in flight), block kb + 1's scores go
@@ -459,7 +483,7 @@ __global__ __launch_bounds__(kThreads, DS <= 16 ? 4 : 2) void fwd_short_bf16_ker
         if (!(kb == 0 && one)) {
           uint32_t e[4];
           entries(wd[(kb + 1) % 3], kb + 1, e);
-          issue_scores<D, NKP>(sTab, e, lane4, sKp, off.k, (kb + 1) & 7, qf, sn);
+          scores(e, kb + 1, sn);
         }
         bf16x8 vop[2][NCB];
         read_v<D>(sVp, off, kb, vop);
@@ -486,7 +510,7 @@ __global__ __launch_bounds__(kThreads, DS <= 16 ? 4 : 2) void fwd_short_bf16_ker
       if (wact) {
         uint32_t e[4];
         entries(wd[0], 0, e);
-        issue_scores<D, NKP>(sTab, e, lane4, sKp, off.k, 0, qf, sa);
+        scores(e, 0, sa);
       }
 #pragma unroll
       for (int kb = 0; kb < ROWS / 32; ++kb) {
@@ -501,7 +525,7 @@ __global__ __launch_bounds__(kThreads, DS <= 16 ? 4 : 2) void fwd_short_bf16_ker
       if (wact) {
         uint32_t e[4];
         entries(wd[0], 0, e);
-        issue_scores<D, NKP>(sTab, e, lane4, sKp, off.k, 0, qf, sc);
+        scores(e, 0, sc);
       }
 #pragma unroll
       for (int kb = 0; kb < ROWS / 32; ++kb) {
@@ -562,22 +586,32 @@ __global__ __launch_bounds__(kThreads, DS <= 16 ? 4 : 2) void fwd_short_bf16_ker
   wait_vmcnt<0>();     // drain the loads issued for the last (repeated) sequence
 }
 
-template <int DS>
+template <int DS, bool WIDE>
 void launch_short_t(const FwdArgs& a, hipStream_t s) {
   const int nseq = a.H / a.hpb;
   const int lgp = a.Sq > 128 ? 0 : (a.Sq > 64 ? 1 : (a.Sq > 32 ? 2 : 3));   // 2^lgp sequences per workgroup
   const int ngroups = (nseq + (1 << lgp) - 1) >> lgp;
   // two workgroups per compute unit where the registers allow four waves per SIMD
-  int slots = (DS <= 16 ? 512 : 256) / a.hpb;
+  int slots = (DS <= 16 && !WIDE ? 512 : 256) / a.hpb;
   if (slots < 1) slots = 1;
   if (slots > ngroups) slots = ngroups;
   const dim3 grid((unsigned)(slots * a.hpb));
   if (!a.spd_dw)
-    hipLaunchKernelGGL((fwd_short_bf16_kernel<DS, true, true>), grid, dim3(kThreads), 0, s, a);
+    hipLaunchKernelGGL((fwd_short_bf16_kernel<DS, true, true, WIDE>), grid, dim3(kThreads), 0, s, a);
   else if (a.Sq % 32 != 0 || a.Sq <= 32)   // keys past N masked (at N <= 32 the whole second block)
-    hipLaunchKernelGGL((fwd_short_bf16_kernel<DS, true, false>), grid, dim3(kThreads), 0, s, a);
+    hipLaunchKernelGGL((fwd_short_bf16_kernel<DS, true, false, WIDE>), grid, dim3(kThreads), 0, s, a);
   else
-    hipLaunchKernelGGL((fwd_short_bf16_kernel<DS, false, false>), grid, dim3(kThreads), 0, s, a);
+    hipLaunchKernelGGL((fwd_short_bf16_kernel<DS, false, false, WIDE>), grid, dim3(kThreads), 0, s, a);
+}
+
+template <bool WIDE>
+void launch_short_d(const FwdArgs& a, int d, hipStream_t s) {
+  switch (d) {
+    case 8: launch_short_t<8, WIDE>(a, s); break;
+    case 16: launch_short_t<16, WIDE>(a, s); break;
+    case 32: launch_short_t<32, WIDE>(a, s); break;
+    default: launch_short_t<64, WIDE>(a, s); break;
+  }
 }
 
 }  // namespace
@@ -586,17 +620,14 @@ bool fwd_short_applies(const FwdArgs& a, int d) {
   // (a group of up to 8 sequences is read through one resource of at most
   // 2^30 bytes)
   return !a.accumulate && a.row_off == 0 && a.col_off == 0 && a.Sq == a.Sk && a.Sq >= 1 && a.Sq <= 256 &&
-         a.n_buckets <= 127 && a.hpb >= 1 && a.H % a.hpb == 0 &&
-         (int64_t)8 * a.hpb * a.Sq * d * 2 < ((int64_t)1 << 30);
+         a.hpb >= 1 && a.H % a.hpb == 0 && (int64_t)8 * a.hpb * a.Sq * d * 2 < ((int64_t)1 << 30);
 }
 
 hipError_t launch_fwd_short_bf16(const FwdArgs& a, int d, hipStream_t s) {
-  switch (d) {
-    case 8: launch_short_t<8>(a, s); break;
-    case 16: launch_short_t<16>(a, s); break;
-    case 32: launch_short_t<32>(a, s); break;
-    default: launch_short_t<64>(a, s); break;
-  }
+  if (a.n_buckets <= 127)
+    launch_short_d<false>(a, d, s);
+  else
+    launch_short_d<true>(a, d, s);
   return hipGetLastError();
 }
 

@@ -123,8 +123,8 @@ inline SplitCost dkdv_split_cost(int D) {
 // The split ks = 1, 2 or 4 that finishes first, for workgroups of rows1 / ks
 // rows.
 int pick_split(int64_t rows, int64_t cols, int64_t heads, const SplitCost& c);
-// Sequences of at most 256 rows (bf16 in and out, at most 127 buckets): the
-// persistent whole-sequence forward.
+// Sequences of at most 256 rows (bf16 in and out): the persistent
+// whole-sequence forward.
 bool fwd_short_applies(const FwdArgs& a, int d);
 hipError_t launch_fwd_short_bf16(const FwdArgs& a, int d, hipStream_t s);
 // phase: -1 = all stages in order, 0 = prepare, 1 = dK/dV/dtable, 2 = dQ.

@@ -190,22 +190,13 @@ def test_f32_packed_batch(B, H, N, d):
     check_grads("dtable", dict(dtable=to_np(got[3])), dict(dtable=dtab), "f32")
 
 
-@pytest.mark.parametrize("B,H,N,d,first", [
-    (3, 2, 1, 64, 0), (9, 2, 3, 8, 1), (17, 4, 30, 8, 0), (11, 4, 31, 64, 0), (9, 8, 33, 16, 3), (7, 4, 47, 64, 0),
-    (5, 8, 63, 32, 0), (5, 2, 65, 64, 2), (5, 2, 129, 16, 0), (3, 2, 203, 32, 0), (3, 2, 255, 64, 1),
-    (3, 2, 256, 64, 0), (3, 2, 256, 8, 1), (2, 2, 200, 64, 0), (70, 8, 50, 64, 1),
-])
-def test_short_batch_any_size(B, H, N, d, first):
-    """bf16 batches on the whole-sequence kernels: lengths either side of the
-    packing limits, of the 32-key block and of the dword, head dim 64, and spd
-    matrices that start at an odd byte; several groups per workgroup."""
+def run_short_batch(B, H, N, d, first, nb):
     g = np.random.default_rng(N * 10 + d)
-    nb = 12
-    spd = g.integers(0, nb + 2, size=(B, N, N)).astype(np.uint8)
+    spd = g.integers(0, min(256, nb + 2), size=(B, N, N)).astype(np.uint8)
     q, k, v, do = (synth.round_bf16(g.standard_normal((B, H, N, d)).astype(np.float32)) for _ in range(4))
     table = (g.standard_normal((H, nb)) * 0.5).astype(np.float32)
     scale = 1.0 / np.sqrt(d)
-    say(f"short bf16 B={B} H={H} N={N} d={d} first={first}")
+    say(f"short bf16 B={B} H={H} N={N} d={d} first={first} nb={nb}")
     bf = torch.bfloat16
     Q, K, V, dO, T = to_dev(q, bf), to_dev(k, bf), to_dev(v, bf), to_dev(do, bf), to_dev(table)
     buf = to_dev(np.concatenate([np.zeros(first, np.uint8), spd.ravel()]), torch.uint8)
@@ -228,3 +219,27 @@ def test_short_batch_any_size(B, H, N, d, first):
         check_grads(f"graph {b}", dict(dq=to_np(got[0][b]), dk=to_np(got[1][b]), dv=to_np(got[2][b])),
                     dict(dq=ref[0], dk=ref[1], dv=ref[2]), "bf16")
     check_grads("dtable", dict(dtable=to_np(got[3])), dict(dtable=sum(r[3] for r in refs)), "bf16")
+
+
+@pytest.mark.parametrize("B,H,N,d,first", [
+    (3, 2, 1, 64, 0), (9, 2, 3, 8, 1), (17, 4, 30, 8, 0), (11, 4, 31, 64, 0), (9, 8, 33, 16, 3), (7, 4, 47, 64, 0),
+    (5, 8, 63, 32, 0), (5, 2, 65, 64, 2), (5, 2, 129, 16, 0), (3, 2, 203, 32, 0), (3, 2, 255, 64, 1),
+    (3, 2, 256, 64, 0), (3, 2, 256, 8, 1), (2, 2, 200, 64, 0), (70, 8, 50, 64, 1),
+])
+def test_short_batch_any_size(B, H, N, d, first):
+    """bf16 batches on the whole-sequence kernels: lengths either side of the
+    packing limits, of the 32-key block and of the dword, head dim 64, and spd
+    matrices that start at an odd byte; several groups per workgroup."""
+    run_short_batch(B, H, N, d, first, 12)
+
+
+@pytest.mark.parametrize("B,H,N,d,first,nb", [
+    (3, 2, 1, 64, 0, 256), (17, 4, 30, 8, 0, 128), (11, 4, 31, 64, 1, 256), (9, 8, 33, 16, 3, 200), (9, 4, 32, 32, 0, 256),
+    (5, 8, 63, 32, 0, 129), (5, 4, 64, 8, 0, 256), (5, 2, 100, 16, 0, 256), (5, 2, 128, 64, 0, 255), (5, 2, 129, 16, 2, 256),
+    (3, 2, 203, 32, 0, 200), (3, 2, 255, 64, 1, 256), (3, 2, 256, 64, 0, 256), (3, 2, 256, 8, 0, 200),
+    (70, 8, 50, 64, 1, 256),
+])
+def test_short_batch_many_buckets(B, H, N, d, first, nb):
+    """The same with 128 to 256 buckets: a table entry for every byte value, the
+    keys past N masked in the sequence's last block."""
+    run_short_batch(B, H, N, d, first, nb)
