@@ -123,8 +123,12 @@ def _ptr(x) -> int | None:
 
 def _stream(stream) -> int | None:
     # the raw handle of torch.cuda.current_stream(), without the Stream object
+    # where this torch has the (private) call for it
     if stream is None:
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if raw is None:
+            return torch.cuda.current_stream().cuda_stream
+        return raw(torch.cuda.current_device())
     return stream.cuda_stream
 
 

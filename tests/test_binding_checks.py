@@ -185,3 +185,12 @@ def test_merge_rejects():
         gt.gt_attn_merge(z(P, H, S, D), lp)
     with pytest.raises(ValueError, match="out must have shape"):
         gt.gt_attn_merge(op, lp, out=z(H, S, 16))
+
+
+def test_current_stream_without_the_private_call(monkeypatch):
+    """A torch without the private raw-stream call: the public one is used."""
+    class Stream:
+        cuda_stream = 7
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: Stream)
+    assert gt._stream(None) == 7 and gt._stream(Stream) == 7

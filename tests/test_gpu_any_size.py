@@ -234,8 +234,9 @@ def test_short_batch_any_size(B, H, N, d, first):
 
 
 @pytest.mark.parametrize("B,H,N,d,first,nb", [
-    (3, 2, 1, 64, 0, 256), (17, 4, 30, 8, 0, 128), (11, 4, 31, 64, 1, 256), (9, 8, 33, 16, 3, 200), (9, 4, 32, 32, 0, 256),
-    (5, 8, 63, 32, 0, 129), (5, 4, 64, 8, 0, 256), (5, 2, 100, 16, 0, 256), (5, 2, 128, 64, 0, 255), (5, 2, 129, 16, 2, 256),
+    (3, 2, 1, 64, 0, 256), (17, 4, 30, 8, 0, 128), (11, 4, 31, 64, 1, 256), (9, 8, 33, 16, 3, 200),
+    (9, 4, 32, 32, 0, 256), (5, 8, 63, 32, 0, 129), (5, 4, 64, 8, 0, 256), (5, 2, 100, 16, 0, 256),
+    (5, 2, 128, 64, 0, 255), (5, 2, 129, 16, 2, 256),
     (3, 2, 203, 32, 0, 200), (3, 2, 255, 64, 1, 256), (3, 2, 256, 64, 0, 256), (3, 2, 256, 8, 0, 200),
     (70, 8, 50, 64, 1, 256),
 ])
