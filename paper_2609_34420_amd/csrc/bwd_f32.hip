@@ -103,6 +103,7 @@ __global__ __launch_bounds__(kThreadsF, 1) void bwd_dq_f32_kernel(BwdArgs a) {
   const int lane = tid & 63;
   const int col = lane & 31, g = lane >> 5;
   const PlaceF32<S, P, BwdArgs> pl(a, a.Sq);
+  if (pl.none) return;
   const int h = pl.h, ks = pl.ks, gw = pl.gw;
   const int64_t qbase = pl.row0;
   const int64_t i = qbase + col;
@@ -249,6 +250,7 @@ __global__ __launch_bounds__(kThreadsF, 1) void bwd_dkdv_f32_kernel(BwdArgs a) {
   const int lane = tid & 63, wave = wave_id();
   const int col = lane & 31, g = lane >> 5;
   const PlaceF32<S, P, BwdArgs> pl(a, a.Sk);
+  if (pl.none) return;
   const int h = pl.h, ks = pl.ks, gw = pl.gw;
   const int64_t key0 = pl.row0;                  // the wave's first key
   const int64_t j = key0 + col;

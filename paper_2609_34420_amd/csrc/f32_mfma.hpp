@@ -62,6 +62,11 @@ struct SplitF32 {
   static_assert(KB >= 1, "a block per wave");
 };
 
+// Workgroups in a row of the grid. A launch has fewer than 2^32 threads per
+// dimension, 2^23 of these workgroups (N = 1 with 8.4 million heads, say), so
+// more of them take further rows, the last one partly filled.
+constexpr int64_t kGridRow = (int64_t)1 << 22;
+
 // A workgroup's place in the grid: the head and first stationary row of this
 // wave, and the sequences [s0, s0 + ns) that its P groups take (head hh).
 template <typename S, int P, typename Args>
@@ -69,13 +74,17 @@ struct PlaceF32 {
   int grp, gw, ks, h, h0, ns;
   int64_t row0;
   bool mine;                                         // the group has a sequence
+  bool none;                                         // the workgroup has no work
   __device__ __forceinline__ PlaceF32(const Args& a, int64_t rows) {
     const int wave = wave_id();
+    const int64_t wg = blockIdx.y * kGridRow + blockIdx.x;
     grp = S::NG == 1 ? 0 : wave / S::NGW;
     gw = S::NG == 1 ? wave : wave % S::NGW;
     if constexpr (P > 1) {
       const int nseq = a.H / a.hpb;
-      const int64_t lid = xcd_remap(blockIdx.x, (int64_t)((nseq + P - 1) / P) * a.hpb);
+      const int64_t total = (int64_t)((nseq + P - 1) / P) * a.hpb;
+      none = wg >= total;
+      const int64_t lid = xcd_remap(none ? 0 : wg, total);
       const int s0 = (int)(lid / a.hpb) * P, hh = (int)(lid % a.hpb);
       ns = nseq - s0 < P ? nseq - s0 : P;
       mine = grp < ns;
@@ -84,7 +93,9 @@ struct PlaceF32 {
       ks = 0;
       row0 = (int64_t)gw * 32;
     } else {
-      const int64_t lid = xcd_remap(blockIdx.x, (rows + S::ROWS - 1) / S::ROWS * a.H);
+      const int64_t total = (rows + S::ROWS - 1) / S::ROWS * a.H;
+      none = wg >= total;
+      const int64_t lid = xcd_remap(none ? 0 : wg, total);
       h = h0 = (int)(lid % a.H);
       ns = 1;
       mine = true;
@@ -294,8 +305,9 @@ __device__ __forceinline__ void combine_groups(float* buf, int ks, int gw, f32x1
 // Grid of a kernel over `rows` stationary rows of every head.
 template <typename S, int P, typename Args>
 dim3 grid_f32(const Args& a, int64_t rows) {
-  if (P > 1) return dim3((unsigned)((a.H / a.hpb + P - 1) / P * a.hpb));
-  return dim3((unsigned)((rows + S::ROWS - 1) / S::ROWS * a.H));
+  const int64_t total = P > 1 ? (int64_t)(a.H / a.hpb + P - 1) / P * a.hpb : (rows + S::ROWS - 1) / S::ROWS * a.H;
+  if (total <= kGridRow) return dim3((unsigned)total);
+  return dim3((unsigned)kGridRow, (unsigned)((total + kGridRow - 1) / kGridRow));
 }
 
 // Runs launch with the split that suits `rows` stationary rows against `cols`:

@@ -35,6 +35,7 @@ __global__ __launch_bounds__(kThreadsF, 1) void fwd_f32_kernel(FwdArgs a) {
   const int lane = threadIdx.x & 63;
   const int col = lane & 31, g = lane >> 5;
   const PlaceF32<S, P, FwdArgs> pl(a, a.Sq);
+  if (pl.none) return;
   const int h = pl.h, ks = pl.ks, gw = pl.gw;
   const int64_t qbase = pl.row0;
   const int64_t i = qbase + col;

@@ -244,3 +244,23 @@ def test_short_batch_many_buckets(B, H, N, d, first, nb):
     """The same with 128 to 256 buckets: a table entry for every byte value, the
     keys past N masked in the sequence's last block."""
     run_short_batch(B, H, N, d, first, nb)
+
+
+def test_f32_more_heads_than_a_grid_row():
+    """fp32, one node and more heads than a launch has workgroups of 512 threads
+    in one dimension: O = V and LSE = the score; dV = dO and no other gradient."""
+    H, d = (1 << 23) + 5, 8
+    say(f"heads {H}")
+    g = torch.Generator(device=DEV)
+    g.manual_seed(0)
+    q, k, v, do = (torch.randn((H, 1, d), device=DEV, generator=g) for _ in range(4))
+    T = torch.randn((H, 2), device=DEV, generator=g)
+    S = torch.ones((1, 1), device=DEV, dtype=torch.uint8)
+    o, l = gt.gt_attn_fwd(q, k, v, S, T, scale=0.5)
+    assert torch.equal(o, v)
+    ref = 0.5 * (q.double() * k.double()).sum(2) + T[:, 1:]
+    assert float((l.double() - ref).abs().max()) <= 1e-5
+    dq, dk, dv, dt = gt.gt_attn_bwd(q, k, v, S, T, o, l, do, scale=0.5)
+    # P is 1 up to the rounding of the score against LSE, dS the rounding of dO.(V - O)
+    assert float((dv - do).abs().max()) <= 1e-4
+    assert max(float(x.abs().max()) for x in (dq, dk, dt)) <= 1e-3
