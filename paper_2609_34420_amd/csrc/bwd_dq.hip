@@ -23,7 +23,9 @@
 // key groups' dQ partials are added through LDS at the end, in a fixed order.
 // H = 8, d = 64: N = 4000 (H = 4) 97 / 61 / 40 us with KS = 1 / 2 / 4, N = 2708
 // 71 / 46 / 56, N = 16384 870 / 1001 / 1105. Sizes that are no multiple of 16
-// took byte loads before: N = 7651 1244 -> 218 us, N = 2708 at d = 16 355 -> 30.
+// took byte loads before: N = 7651 1244 -> 209 us, N = 2708 at d = 16 355 -> 27.
+// (At d = 64 kBytes spills 8 registers unsplit and 18 with two groups, kRagged 5
+// with two, none with four.)
 #include <type_traits>
 
 #include "common.hpp"

@@ -9,13 +9,18 @@
 // most 2^-54 of the bound, without a bias. (A row of dO and one of V 1e4 times
 // the others', N = 1500, d = 64: in the buckets that row does not hold dtable is
 // off by 8e-7 of 64 bits, 8e-4 with the terms rounded down; dO 1e6 times 4e-6
-// and 7e-3.) And a row's terms sum to at most the bound in magnitude (the P of a row sum
-// to at most 1). Neither is taken for granted: a term whose dO_i.V_j - Dlt_i is
-// not below 2^(53 - F) (infinite or NaN inputs, rows whose squared norm
-// overflows: the bound leaves their block of 256 out) and, once the P of a lane's half row
-// sum to more than 1.5, all its further terms (an LSE that is not the inputs')
-// are added to dtable itself as floats. So each of a workgroup's 512 lanes adds
-// less than 1.5 2^53 and the sums stay below 2^63.
+// and 7e-3.) And a row's terms sum to at most the bound in magnitude (the P of a
+// row sum to at most 1). Neither is taken for granted: a term whose dO_i.V_j -
+// Dlt_i is not below 2^(53 - F) (infinite or NaN inputs, rows whose squared norm
+// overflows: the bound leaves their block of 256 out) and, once the P of a
+// lane's half row sum to more than 1.5, all its further terms (an LSE that is
+// not the inputs') are added to dtable itself as floats. So each of a
+// workgroup's 512 lanes adds less than 1.5 2^53 and the sums stay below 2^63.
+//
+// Registers: at head dim 64 a tile in flight and two operands fill the 256 of a
+// wave. dK/dV spills 6 and 16 of them with one and two query groups (the form
+// of a graph of a few thousand nodes), 46 with four, 34 and 98 in packed batches;
+// dQ up to 9 in packed batches.
 #include "f32_mfma.hpp"
 
 namespace gt {

@@ -45,7 +45,9 @@
 // Before these kernels took every size, an N that is no multiple of 16 went
 // byte by byte: N = 7651 2298 us, N = 2708 at d = 16 677 us, now 175 and 30.
 //
-// Any size and alignment: see SpdRows in stage.hpp.
+// Any size and alignment: see SpdRows in stage.hpp. At d = 64 the five dwords of
+// kBytes do not all fit the registers: it spills 5 unsplit and 11 with two
+// groups (kRagged 2), none with four.
 #pragma once
 #include <type_traits>
 

@@ -191,29 +191,31 @@ __device__ __forceinline__ void softmax_first(const f32x16& s, const bf16x8 (&vo
   }
 }
 
-// Persistent forward for sequences of at most 256 rows with at most 127
-// buckets (bf16 in and out, head dims 8, 16, 32 on 32-wide tiles, 64 on its
-// own). Each wave owns 32 queries, and the sequence's K and V (all rows) sit
-// in LDS: one pair of barriers per sequence instead of one barrier per key
-// tile. At N > 128 a workgroup covers one sequence; shorter ones are packed, 2, 4 or 8 sequences of the
-// head at once (N <= 128, 64, 32), each in its own slice of the K and V
-// rows with 4, 2 or 1 waves. The per-lane bias table holds the byte values
-// 0..127 (bytes of 128 or more are mapped to the padding entry 127, bias 0)
-// and an entry of -inf (128) that masks the keys past N: with K and V that
-// is about 71 KB, so two workgroups share a compute unit and every SIMD
-// runs four waves. The workgroups are persistent: workgroup w takes head
-// (w mod hpb) of every (G / hpb)-th group of sequences, fills the table
-// once, and loads the next group's K, V and Q rows into registers while it
-// computes the current one. spd words stream two key blocks ahead across
-// groups (read 16 bytes at a time from 4-byte aligned offsets, through a
-// resource that ends with the sequence's matrix); the score product of key
-// block kb + 1 is issued before the softmax of block kb. TAIL: keys past N
-// in the last block (N not a multiple of 32, or N <= 32). ANY: spd rows at any
-// address, loaded as the 5 dwords that hold each group and aligned in registers
-// (N not a multiple of 4; TAIL goes with it). H = 8, against the full-width
-// forward that took these before (its 64 KB table filled per workgroup and one
-// workgroup per compute unit): 512 x 203 nodes, d = 32 206 -> 106 us, 8192 x 30, d = 8
-// 3790 -> 88; d = 64: 512 x 256 247 -> 177, 4000 x 33 2242 -> 148.
+// Persistent forward for sequences of at most 256 rows (bf16 in and out, head
+// dims 8, 16, 32 on 32-wide tiles, 64 on its own). Each wave owns 32 queries,
+// and the sequence's K and V (all rows) sit in LDS: one pair of barriers per
+// sequence instead of one barrier per key tile. At N > 128 a workgroup covers
+// one sequence; shorter ones are packed, 2, 4 or 8 sequences of the head at once
+// (N <= 128, 64, 32), each in its own slice of the K and V rows with 4, 2 or 1
+// waves. Up to 127 buckets the per-lane bias table holds the byte values 0..127
+// (bytes of 128 or more are mapped to the padding entry 127, bias 0) and an
+// entry of -inf (128) that masks the keys past N. With K and V that is 68 KB on
+// the 32-wide tiles, so at head dims 8 and 16 two workgroups share a compute
+// unit and every SIMD runs four waves; at 32 the registers and at 64 the 104 KB
+// allow one. The workgroups are persistent: workgroup w takes head (w mod hpb)
+// of every (G / hpb)-th group of sequences, fills the table once, and loads the
+// next group's K, V and Q rows into registers while it computes the current one.
+// spd words stream two key blocks ahead across groups (read 16 bytes at a time
+// from 4-byte aligned offsets, through a resource that ends with the sequence's
+// matrix); the score product of key block kb + 1 is issued before the softmax of
+// block kb. TAIL: keys past N in the last block (N not a multiple of 32, or N <=
+// 32). ANY: spd rows at any address, loaded as the 5 dwords that hold each group
+// and aligned in registers (N not a multiple of 4; TAIL goes with it; at head
+// dims 8 and 16 the three word sets in flight leave 32 registers to spill at
+// four waves per SIMD, 2 in the aligned TAIL form, 3 at d = 8 without). H = 8, against the
+// full-width forward that took these before (its 64 KB table filled per
+// workgroup and one workgroup per compute unit): 512 x 203 nodes, d = 32 206 -> 106
+// us, 8192 x 30, d = 8 3790 -> 88; d = 64: 512 x 256 247 -> 177, 4000 x 33 2242 -> 148.
 // WIDE: 128 to 256 buckets. The table then has an entry for every byte value
 // (64 KB, one workgroup per compute unit at every head dim), and the scores of
 // keys past N start from -inf by a select in the sequence's last block. 1024 x
@@ -236,7 +238,7 @@ __global__ __launch_bounds__(kThreads, DS <= 16 && !WIDE ? 4 : 2) void fwd_short
   constexpr int NKP = XP ? 2 : NKS;             // 16-feature chunks of the score product
   // alternating score sets where registers allow: at d >= 32 (one workgroup
   // per compute unit) and at d = 8 without a partial key block; elsewhere
-  // the copy keeps four waves per SIMD without spilling
+  // the copy keeps the sets within four waves per SIMD
   constexpr bool ALT = DS >= 32 || XP;
   // Padding rows (zero): the K rows of block nkb mod 8, read past the last
   // block of a sequence (the product is never used)

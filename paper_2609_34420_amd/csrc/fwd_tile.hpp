@@ -1,8 +1,8 @@
 // Building blocks of the bf16 forward kernels (the full forward / ring step
-// in fwd.hip and the persistent short-sequence forward in fwd_short.hip):
+// in fwd_mfma.hpp and the persistent short-sequence forward in fwd_short.hip):
 // the per-lane softmax state, the operand offsets, the score product with
 // the bias as its accumulator start, and the softmax of one 32 x 32 block
-// with its P^T V product (the lazy reference is described in fwd.hip).
+// with its P^T V product (the lazy reference is described in fwd_mfma.hpp).
 #pragma once
 #include "common.hpp"
 #include "stage.hpp"

@@ -105,7 +105,8 @@ def test_key_stationary_table_and_histogram_128():
 
 
 def test_key_stationary_table_and_histogram_256():
-    """Past 127 buckets: 16 copies (lane & 15) of a 256-bucket layout,
+    """Past 127 buckets where the tiles take the whole 64 KiB below the table
+    (d = 64, four query groups): 16 copies (lane & 15) of a 256-bucket layout,
     entry address (b << 7) | copy offset | base."""
     tab_base, ent = 1 << 16, 256 * 16
     for lane in range(64):
@@ -115,6 +116,23 @@ def test_key_stationary_table_and_histogram_256():
             idx = (a - tab_base) // 8
             assert 0 <= idx < ent and idx == b * 16 + (lane & 15)
             assert a + ent * 8 < tab_base + 2 * ent * 8
+
+
+def test_key_stationary_table_and_histogram_256_halved():
+    """Past 127 buckets elsewhere: 32 copies (lane & 31), the histogram from 64
+    KiB at the permuted address, the 4-byte table from 32 KiB at half of it."""
+    hist_base, tab_base, ent = 1 << 16, 1 << 15, 256 * 32
+    seen = set()
+    for lane in range(64):
+        cpyb = (lane & 31) * 8 | hist_base
+        for b in range(256):
+            a = perm(b, cpyb, 0x0C020400)
+            assert (a - hist_base) // 8 == b * 32 + (lane & 31) < ent
+            t = a >> 1
+            assert t % 4 == 0 and (t - tab_base) // 4 == b * 32 + (lane & 31)
+            assert tab_base <= t < tab_base + ent * 4 <= hist_base
+            seen.add(a)
+    assert len(seen) == ent
 
 
 def test_histogram_fixed_point_range():
