@@ -103,6 +103,7 @@ struct DkdvTable {
   static constexpr int ENT = NB * CPY;            // entry (b, c) = b * CPY + c
   uint2 tabw[ENT];                  // table copies (fp32 bits, 8-byte stride)
   unsigned long long hist[ENT];     // gradient histogram copies, same index
+  __device__ __forceinline__ void set_table(int t, float v) { tabw[t] = make_uint2(__float_as_uint(v), 0u); }
   static constexpr int PER16 = 2;                 // entries in 16 bytes
   __device__ __forceinline__ void set16(int t, float v) {
     reinterpret_cast<uint4*>(tabw)[t] = make_uint4(__float_as_uint(v), 0u, __float_as_uint(v), 0u);
@@ -583,15 +584,27 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dkdv_bf16_kernel(BwdArgs a) {
   const int64_t j = kblk * kBK + (QS == 1 ? wave : wave % (kNW / QS)) * 32 + col;
   const bool jok = j < a.Sk;
 
-  // 16 bytes per store; the histogram of the table's buckets only (what other
-  // byte values add is not read). Sequences of 64 rows, 200 buckets, d = 64, 32768
-  // heads: 1415 us with an entry per store and the whole histogram cleared, 1193 so.
-  for (int t = tid; t < Table::ENT / Table::PER16; t += kThreads) {
-    const int bkt = t * Table::PER16 / CPY;
-    sm.t.set16(t, bkt < a.n_buckets ? a.table[(int64_t)table_row(a, h) * a.n_buckets + bkt] * kLog2e : 0.0f);
+  // Past 127 buckets 16 bytes per store, and the histogram of the table's buckets
+  // only (what other byte values add is not read): sequences of 64 rows, 200
+  // buckets, d = 64, 32768 heads 1415 us with an entry per store and the whole
+  // histogram cleared, 1198 so. The 128-bucket layout is half as large and keeps
+  // the single stores: with the others the compiler's registers in the main
+  // loop come out worse (headline shape: 90.2 ms, 93.1).
+  if constexpr (NB <= 128) {
+    for (int t = tid; t < Table::ENT; t += kThreads) {
+      const int bkt = t / CPY;
+      const float tv = (bkt < a.n_buckets) ? a.table[(int64_t)table_row(a, h) * a.n_buckets + bkt] * kLog2e : 0.0f;
+      sm.t.set_table(t, tv);
+      hist[t] = 0ull;
+    }
+  } else {
+    for (int t = tid; t < Table::ENT / Table::PER16; t += kThreads) {
+      const int bkt = t * Table::PER16 / CPY;
+      sm.t.set16(t, bkt < a.n_buckets ? a.table[(int64_t)table_row(a, h) * a.n_buckets + bkt] * kLog2e : 0.0f);
+    }
+    for (int t = tid; t < Table::ENT / 2; t += kThreads)
+      if (t < a.n_buckets * CPY / 2) reinterpret_cast<uint4*>(hist)[t] = make_uint4(0u, 0u, 0u, 0u);
   }
-  for (int t = tid; t < a.n_buckets * CPY / 2; t += kThreads)
-    reinterpret_cast<uint4*>(hist)[t] = make_uint4(0u, 0u, 0u, 0u);
 
   // Fixed-point exponent F of this head: (max|dO| max|V| + max|Dlt|) 2^F
   // <= 2^30 (a 1.5 % margin covers the rounding of P and of the products).
