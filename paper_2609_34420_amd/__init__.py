@@ -121,14 +121,17 @@ def _ptr(x) -> int | None:
     return None if x is None else x.data_ptr()
 
 
+# (private to torch, so it may be missing)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream) -> int | None:
     # the raw handle of torch.cuda.current_stream(), without the Stream object
-    # where this torch has the (private) call for it
+    # where this torch has the call for it
     if stream is None:
-        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-        if raw is None:
+        if _raw_stream is None:
             return torch.cuda.current_stream().cuda_stream
-        return raw(torch.cuda.current_device())
+        return _raw_stream(torch.cuda.current_device())
     return stream.cuda_stream
 
 

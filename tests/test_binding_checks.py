@@ -191,6 +191,6 @@ def test_current_stream_without_the_private_call(monkeypatch):
     """A torch without the private raw-stream call: the public one is used."""
     class Stream:
         cuda_stream = 7
-    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(gt, "_raw_stream", None)
     monkeypatch.setattr(torch.cuda, "current_stream", lambda: Stream)
     assert gt._stream(None) == 7 and gt._stream(Stream) == 7
