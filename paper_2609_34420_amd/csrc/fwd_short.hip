@@ -191,6 +191,23 @@ __device__ __forceinline__ void softmax_first(const f32x16& s, const bf16x8 (&vo
   }
 }
 
+// issue_scores with the keys at or past jrem (relative to the block) started
+// from -inf.
+template <int D, int NK>
+__device__ __forceinline__ void issue_scores_masked(const float* tab, const uint32_t (&w)[4], uint32_t lane4,
+                                                    const uint16_t* sK, const int (&koff)[D / 16], int kb,
+                                                    const bf16x8 (&q)[D / 16], int jrem, f32x16& s) {
+  load_bias(tab, w, lane4, s);
+  if (jrem < 32) {
+    uint32_t left = (uint32_t)(jrem - 16 * (int)((threadIdx.x >> 5) & 1));   // keys of this lane half
+    opaque(left);                                // (its 16 comparisons are not kept for every block)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] = r < (int)left ? s[r] : -INFINITY;
+  }
+#pragma unroll
+  for (int kc = 0; kc < NK; ++kc) s = mfma32(lds_b128(sK + kb * 32 * D + koff[kc]), q[kc], s);
+}
+
 // Persistent forward for sequences of at most 256 rows (bf16 in and out, head
 // dims 8, 16, 32 on 32-wide tiles, 64 on its own). Each wave owns 32 queries,
 // and the sequence's K and V (all rows) sit in LDS: one pair of barriers per
@@ -219,8 +236,8 @@ __device__ __forceinline__ void softmax_first(const f32x16& s, const bf16x8 (&vo
 // WIDE: 128 to 256 buckets. The table then has an entry for every byte value
 // (64 KB, one workgroup per compute unit at every head dim), and the scores of
 // keys past N start from -inf by a select in the sequence's last block. 1024 x
-// 256 nodes, H = 8, 256 buckets: d = 8 309 us on the full-width kernel, 150 here, d =
-// 64 533 and 350; 4096 x 64, 200 buckets, d = 8: 589 and 74.
+// 256 nodes, H = 8, 256 buckets: d = 8 309 us on the full-width kernel, 144 here, d =
+// 64 533 and 332; 4096 x 64, 200 buckets, d = 8: 589 and 72.
 constexpr int kShortTabEntries = 129;
 template <int DS, bool TAIL, bool ANY, bool WIDE>
 __global__ __launch_bounds__(kThreads, DS <= 16 && !WIDE ? 4 : 2) void fwd_short_bf16_kernel(FwdArgs a) {
@@ -373,8 +390,7 @@ __global__ __launch_bounds__(kThreads, DS <= 16 && !WIDE ? 4 : 2) void fwd_short
     if constexpr (ANY) align_spd5(x, sh);
 #pragma unroll
     for (int u = 0; u < 4; ++u) e[u] = x[u];
-    if constexpr (WIDE) return;
-    if (__any(((e[0] | e[1] | e[2] | e[3]) & 0x80808080u) != 0)) {
+    if (!WIDE && __any(((e[0] | e[1] | e[2] | e[3]) & 0x80808080u) != 0)) {
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         uint32_t x = e[u];
@@ -384,7 +400,7 @@ __global__ __launch_bounds__(kThreads, DS <= 16 && !WIDE ? 4 : 2) void fwd_short
         e[u] = x;
       }
     }
-    if constexpr (TAIL) {
+    if constexpr (TAIL && !WIDE) {
       if constexpr (!ANY) {      // rows on dword boundaries: N is a multiple of 4
 #pragma unroll
         for (int u = 0; u < 4; ++u)
@@ -452,21 +468,6 @@ __global__ __launch_bounds__(kThreads, DS <= 16 && !WIDE ? 4 : 2) void fwd_short
     st.l = 0.0f;
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb) acc[cb] = zero_f32x16();
-    // Scores of key block kb with the bias entries e.
-    auto scores = [&](const uint32_t (&e)[4], int kb, f32x16& s) {
-      if constexpr (WIDE && TAIL) {
-        load_bias(sTab, e, lane4, s);
-        if (kb * 32 + 32 > N) {
-          uint32_t left = (uint32_t)(N - kb * 32 - 16 * g);   // keys of this lane half
-          opaque(left);                          // (its 16 comparisons are not kept for every block)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) s[r] = r < (int)left ? s[r] : -INFINITY;
-        }
-        add_scores<D, NKP>(sKp, off.k, kb & 7, qf, s);
-      } else {
-        issue_scores<D, NKP>(sTab, e, lane4, sKp, off.k, kb & 7, qf, s);
-      }
-    };
     // Key block kb: the words of block kb + 2 are fetched (of the next
     // sequence past the end: one load whatever the source, so the wait for
     // block kb + 1's words leaves it in flight), block kb + 1's scores go
@@ -485,7 +486,10 @@ __global__ __launch_bounds__(kThreads, DS <= 16 && !WIDE ? 4 : 2) void fwd_short
         if (!(kb == 0 && one)) {
           uint32_t e[4];
           entries(wd[(kb + 1) % 3], kb + 1, e);
-          scores(e, kb + 1, sn);
+          if constexpr (WIDE && TAIL)
+            issue_scores_masked<D, NKP>(sTab, e, lane4, sKp, off.k, (kb + 1) & 7, qf, N - (kb + 1) * 32, sn);
+          else
+            issue_scores<D, NKP>(sTab, e, lane4, sKp, off.k, (kb + 1) & 7, qf, sn);
         }
         bf16x8 vop[2][NCB];
         read_v<D>(sVp, off, kb, vop);
@@ -512,7 +516,10 @@ __global__ __launch_bounds__(kThreads, DS <= 16 && !WIDE ? 4 : 2) void fwd_short
       if (wact) {
         uint32_t e[4];
         entries(wd[0], 0, e);
-        scores(e, 0, sa);
+        if constexpr (WIDE && TAIL)
+          issue_scores_masked<D, NKP>(sTab, e, lane4, sKp, off.k, 0, qf, N, sa);
+        else
+          issue_scores<D, NKP>(sTab, e, lane4, sKp, off.k, 0, qf, sa);
       }
 #pragma unroll
       for (int kb = 0; kb < ROWS / 32; ++kb) {
@@ -527,7 +534,10 @@ __global__ __launch_bounds__(kThreads, DS <= 16 && !WIDE ? 4 : 2) void fwd_short
       if (wact) {
         uint32_t e[4];
         entries(wd[0], 0, e);
-        scores(e, 0, sc);
+        if constexpr (WIDE && TAIL)
+          issue_scores_masked<D, NKP>(sTab, e, lane4, sKp, off.k, 0, qf, N, sc);
+        else
+          issue_scores<D, NKP>(sTab, e, lane4, sKp, off.k, 0, qf, sc);
       }
 #pragma unroll
       for (int kb = 0; kb < ROWS / 32; ++kb) {

@@ -105,18 +105,13 @@ __device__ __forceinline__ void softmax_pv(const f32x16& s, const bf16x8 (&vop)[
 // unit's Q^T.
 // NK: the 16-feature chunks that hold data (all D / 16, or fewer when the
 // source rows are narrower than the tile and the rest is zero).
-template <int D, int NK>
-__device__ __forceinline__ void add_scores(const uint16_t* sK, const int (&koff)[D / 16], int kb,
-                                           const bf16x8 (&q)[D / 16], f32x16& s) {
-#pragma unroll
-  for (int kc = 0; kc < NK; ++kc) s = mfma32(lds_b128(sK + kb * 32 * D + koff[kc]), q[kc], s);
-}
 template <int D, int NK, int NW>
 __device__ __forceinline__ void issue_scores(const float* tab, const uint32_t (&w)[NW], uint32_t lane4,
                                              const uint16_t* sK, const int (&koff)[D / 16], int kb,
                                              const bf16x8 (&q)[D / 16], f32x16& s) {
   load_bias(tab, w, lane4, s);
-  add_scores<D, NK>(sK, koff, kb, q, s);
+#pragma unroll
+  for (int kc = 0; kc < NK; ++kc) s = mfma32(lds_b128(sK + kb * 32 * D + koff[kc]), q[kc], s);
 }
 
 template <int D>
