@@ -87,7 +87,7 @@ __device__ __forceinline__ void store4(float* p, float4 v, bool accumulate) {
 // dQ and dtable. Each wave owns 32 queries: S^T = K Q^T and dP^T = V dO^T with
 // the queries on the lanes, dQ^T += K^T dS^T from registers (96 products per
 // 32 x 32 block at head dim 64). N = 3327, H = 8, d = 64: 2382 us on the vector
-// ALUs, 377 here; error of dQ 6.5e-7 -> 6.1e-7, of dtable 9.8e-7 -> 5.8e-7.
+// ALUs, 377 here; error of dQ 6.7e-7 -> 6.3e-7, of dtable 1.1e-6 -> 6.4e-7.
 template <int D, int KS, int P>
 __global__ __launch_bounds__(kThreadsF, 1) void bwd_dq_f32_kernel(BwdArgs a) {
   using S = SplitF32<D, KS, P>;
@@ -234,7 +234,7 @@ __global__ __launch_bounds__(kThreadsF, 1) void bwd_dq_f32_kernel(BwdArgs a) {
 // on the lanes, dV^T += dO^T P and dK^T += Q^T dS from registers (128 products
 // per block at head dim 64). The wave's 32 x 32 spd bytes are loaded row-wise
 // and transposed through LDS as in the bf16 kernel. N = 3327, H = 8, d = 64:
-// 3495 us on the vector ALUs, 473 here; error of dK 6.4e-7 -> 6.1e-7.
+// 3495 us on the vector ALUs, 473 here; error of dK 6.6e-7 -> 6.3e-7.
 template <int D, int KS, int P>
 __global__ __launch_bounds__(kThreadsF, 1) void bwd_dkdv_f32_kernel(BwdArgs a) {
   using S = SplitF32<D, KS, P>;

@@ -190,7 +190,8 @@ __device__ __forceinline__ void product_rows(const float* t, const float (&f)[D 
 // the rows; lanes of rows past a narrow head dim repeat its features (their
 // results are not used). The block's 32 terms are summed on their own and
 // then added: one accumulator over all rows would gather their rounding (N =
-// 3327, d = 64: O off by 9.7e-7 of 64 bits instead of 5.2e-7). A column with
+// 3327, d = 64, 2-norm against 64 bits: O off by 8.0e-7 instead of 3.6e-7, dQ by
+// 9.6e-7 instead of 6.3e-7). A column with
 // keep false takes nothing from the block, whatever its rows hold.
 template <int D>
 __device__ __forceinline__ void product_cols(const float* t, const float (&b)[16], f32x16 (&acc)[kBlocksF<D>],
